@@ -195,6 +195,10 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
   // wave, so each access below is a scalar row base plus the lane's offset
   // (no per-lane 64-bit address arithmetic).
   auto row_off = [&](int i) { return (long long)(jb + i) * J.n + c0; };
+  const float lam = in_vgpr(J.lam), c = in_vgpr(J.c);
+  Radii R = J.R;
+  R.ra = in_vgpr(R.ra);
+  R.sa = in_vgpr(R.sa);
   float4 q[P], r[P];
   float2 b[P];
   bool inside[P];
@@ -269,7 +273,7 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
           up = (j > 0) ? up : zero2;
           left = has_left ? left : zero2;
         }
-        y[i] = proj_c<CONSTR>(dual_to_primal(b[i], r[i], up, left, J.lam), inside[i]);
+        y[i] = proj_c<CONSTR>(dual_to_primal(b[i], r[i], up, left, lam), inside[i]);
       }
     }
     sTop[wave * kRW + lane] = y[0];
@@ -283,9 +287,9 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
         const int j = jb + i;
         const float rx = lane_from_right(y[i].x), rv = lane_from_right(y[i].y);
         const float2 down = (i < P - 1) ? y[i + 1] : down_last;
-        const float4 g = dual_step(r[i], y[i], down, make_float2(rx, rv), J.c,
+        const float4 g = dual_step(r[i], y[i], down, make_float2(rx, rv), c,
                                    !BORDER || j < J.m - 1, has_right);
-        dual_update<KIND>(g, J.R, beta, q[i], r[i]);
+        dual_update<KIND>(g, R, beta, q[i], r[i]);
       }
     }
     if (HIST) {
@@ -317,7 +321,7 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
           up = (j > 0) ? up : zero2;
           left = has_left ? left : zero2;
         }
-        const float2 xv = proj_c<CONSTR>(dual_to_primal(b[i], q[i], up, left, J.lam), inside[i]);
+        const float2 xv = proj_c<CONSTR>(dual_to_primal(b[i], q[i], up, left, lam), inside[i]);
         if (col_out && (!BORDER || j < J.m)) store_nt(J.x + row_off(i) + lane, xv);
       }
     }
