@@ -137,6 +137,13 @@ __device__ __forceinline__ float4 dual_step(float4 r, float2 y, float2 down, flo
   return g;
 }
 
+// The same with the step of each direction given (0 where that difference does
+// not exist; the caller's r is 0 there, so g is too).
+__device__ __forceinline__ float4 dual_step(float4 r, float2 y, float2 down, float2 right, float cv, float ch) {
+  return make_float4(fmaf(cv, y.x - down.x, r.x), fmaf(cv, y.y - down.y, r.y), fmaf(ch, y.x - right.x, r.z),
+                     fmaf(ch, y.y - right.y, r.w));
+}
+
 // Streaming (non-temporal) stores, used for the forward tile's dual state and
 // x: they leave less dirty data in the L2 caches to be written back at the
 // kernel boundary (measured: +2 % at 2048^2). Loads keep the default policy,

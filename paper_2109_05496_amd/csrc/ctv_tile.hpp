@@ -34,6 +34,41 @@ __device__ __forceinline__ float lane_from_right(float v) {  // lane i <- lane i
   return __int_as_float(__builtin_amdgcn_update_dpp(0, __float_as_int(v), 0x130, 0xf, 0xf, true));
 }
 
+// One row of an image, from its first column inside a tile's region on, as a
+// buffer of `bytes` bytes (0 for a row outside the image): the hardware's bounds
+// check returns 0 for loads past it and drops stores, so a tile at the image's
+// border loads and stores without a branch per row, all rows in flight at once.
+// A lane outside the image uses the offset kNoOffset.
+constexpr int kNoOffset = (int)0x80000000;
+template <class T>
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t row_buf(const T* row, int bytes) {
+  return __builtin_amdgcn_make_buffer_rsrc(const_cast<T*>(row), (short)0, bytes, 0x00020000);
+}
+typedef int vint4 __attribute__((ext_vector_type(4)));
+typedef int vint2 __attribute__((ext_vector_type(2)));
+__device__ __forceinline__ float4 buf_ld4(__amdgpu_buffer_rsrc_t r, int off) {
+  const vint4 v = __builtin_amdgcn_raw_buffer_load_b128(r, off, 0, 0);
+  return make_float4(__int_as_float(v.x), __int_as_float(v.y), __int_as_float(v.z), __int_as_float(v.w));
+}
+__device__ __forceinline__ float2 buf_ld2(__amdgpu_buffer_rsrc_t r, int off) {
+  const vint2 v = __builtin_amdgcn_raw_buffer_load_b64(r, off, 0, 0);
+  return make_float2(__int_as_float(v.x), __int_as_float(v.y));
+}
+__device__ __forceinline__ bool buf_ld_mask(__amdgpu_buffer_rsrc_t r, int off) {
+  return __builtin_amdgcn_raw_buffer_load_b8(r, off, 0, 0) != 0;
+}
+// AUX: cache policy bits (2 = non-temporal)
+template <int AUX = 0>
+__device__ __forceinline__ void buf_st4(__amdgpu_buffer_rsrc_t r, int off, float4 v) {
+  const vint4 u = {__float_as_int(v.x), __float_as_int(v.y), __float_as_int(v.z), __float_as_int(v.w)};
+  __builtin_amdgcn_raw_buffer_store_b128(u, r, off, 0, AUX);
+}
+template <int AUX = 0>
+__device__ __forceinline__ void buf_st2(__amdgpu_buffer_rsrc_t r, int off, float2 v) {
+  const vint2 u = {__float_as_int(v.x), __float_as_int(v.y)};
+  __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, AUX);
+}
+
 // Bits [max(a, 0), min(b, n)) set: the rows i of a wave with a <= i < b.
 __device__ __forceinline__ unsigned row_bits(int a, int b, int n) {
   a = min(max(a, 0), n);
