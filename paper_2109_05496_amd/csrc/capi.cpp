@@ -108,7 +108,51 @@ void clamp_fuse(Tiling* t, int iters) {
   t->T = std::max(t->T, 1);
 }
 
-ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* out, bool use_tuned) {
+// Tile shape and fusion depth for a run of `iters` iterations where one tile per
+// CU covers the problem. A launch's time is then not bandwidth but the latency of
+// one tile, fixed + step T for T iterations (microseconds, fitted to launches of
+// T = 4 .. 14 on MI355X, within 6 %): smaller tiles start sooner and have fewer
+// rows to iterate, deeper fusion saves launches, and a larger halo is free as long
+// as the tiles do not outnumber the CUs. A second tile on a CU costs at least half
+// a launch more, so only shapes and depths that stay within one are considered,
+// against the default (8 x 8, T = 8) with the tiles it has. Measured, default ->
+// this choice, per iteration: 128^2 1.99 -> 1.09 us, 512^2 2.03 -> 1.51,
+// 12 x 150 x 203 1.98 -> 1.71, 700^2 2.23 -> 1.99. Choosing by such a model among
+// two and more tiles per CU too was up to 10 % slower than the default (1000 x 1501
+// 293 -> 326 us), so the line is drawn at one.
+static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
+  struct Cost {
+    int waves, rows;
+    double fixed, step;
+  };
+  static const Cost costs[] = {{8, 8, 6.5, 1.20}, {12, 4, 5.5, 0.92}, {8, 4, 4.7, 0.81}, {16, 4, 7.2, 1.05}};
+  constexpr int kCus = 256, kMaxT = 14;
+  const int images = std::min(batch, kPlainChunk);
+  auto per_cu = [&](const Cost& c, int T) {
+    const long long ow = 64 - 2 * T, oh = c.waves * c.rows - 2 * T;
+    return (((n + ow - 1) / ow) * ((m + oh - 1) / oh) * images + kCus - 1) / kCus;
+  };
+  auto launches = [&](int T) { return (iters + T - 1) / T; };
+  const long long k = iters > 0 ? per_cu(costs[0], std::min(8, iters)) : 0;
+  if (k < 1 || k > 3) return;
+  const int Td = (iters + launches(8) - 1) / launches(8);
+  double best = launches(8) * (3.5 + 3.0 * k + Td * (0.35 + 0.85 * k));
+  // an image inside one 8 x 8 tile: the single-tile kernel's one launch
+  if (m <= 64 && n <= 64) best = (iters + kFlowMaxIters - 1) / kFlowMaxIters * 5.0 + 1.18 * iters;
+  for (const Cost& c : costs)
+    for (int T = 1; T <= std::min({kMaxT, iters, c.waves * c.rows / 2 - 2}); ++T) {
+      if ((iters + launches(T) - 1) / launches(T) != T || per_cu(c, T) > 1) continue;
+      const double us = launches(T) * (c.fixed + c.step * T);
+      if (us < best) {
+        best = us;
+        out->shape.waves = c.waves;
+        out->shape.rows_per_thread = c.rows;
+        out->T = T;
+      }
+    }
+}
+
+ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* out, bool use_tuned, int run) {
   Tiling t;
   t.shape.waves = 8;
   t.shape.rows_per_thread = 8;
@@ -123,7 +167,10 @@ ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* o
       return fail(CTV_ERR_INVALID_ARG, "unsupported tile shape");
   } else if (use_tuned && p->fuse == 0) {
     Tiling tuned;
-    if (tuned_lookup(plain_tune_key(p, batch, m, n), &tuned) && valid_tile_shape(tuned.shape)) t = tuned;
+    if (tuned_lookup(plain_tune_key(p, batch, m, n), &tuned) && valid_tile_shape(tuned.shape))
+      t = tuned;
+    else
+      small_tiling(m, n, batch, run > 0 ? std::min(run, p->iters) : p->iters, &t);
   }
   if (p->fuse > 0) t.T = p->fuse;
   clamp_fuse(&t, p->iters);
@@ -277,7 +324,7 @@ ctv_status ctv_denoise(const ctv_params* p, int32_t batch, int32_t m, int32_t n,
       reinterpret_cast<char*>(flow_mem) +
       align_up((size_t)flow_ints(std::min(batch, kPlainChunk), m, n, flow_max_halo()) * 4));
   Tiling tl;
-  st = choose_tiling(p, m, n, batch, &tl, p->schedule != CTV_S_FLOW);
+  st = choose_tiling(p, m, n, batch, &tl, p->schedule != CTV_S_FLOW, ckpt_every);
   if (st) return st;
   const bool flow_ok = ckpt_every == 0 && p->iters > 0 && tl.shape.waves == 8 && tl.shape.rows_per_thread == 8;
   if (p->schedule == CTV_S_FLOW && !flow_ok)
