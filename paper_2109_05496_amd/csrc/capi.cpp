@@ -108,24 +108,25 @@ void clamp_fuse(Tiling* t, int iters) {
   t->T = std::max(t->T, 1);
 }
 
-// Tile shape and fusion depth for a run of `iters` iterations where one tile per
-// CU covers the problem. A launch's time is then not bandwidth but the latency of
+// Tile shape and fusion depth for a run of `iters` iterations where one or two
+// tiles per CU cover the problem. A launch's time is then not bandwidth but the latency of
 // one tile, fixed + step T for T iterations (microseconds, fitted to launches of
 // T = 4 .. 14 on MI355X, within 6 %): smaller tiles start sooner and have fewer
 // rows to iterate, deeper fusion saves launches, and a larger halo is free as long
-// as the tiles do not outnumber the CUs. A second tile on a CU costs at least half
-// a launch more, so only shapes and depths that stay within one are considered,
-// against the default (8 x 8, T = 8) with the tiles it has. Measured, default ->
+// as the tiles do not outnumber the CUs. The 12 x 4 and 8 x 4 tiles are also
+// considered with two tiles per CU (both resident). These compete against the
+// default (8 x 8, T = 8) with the tiles it has. Measured, default ->
 // this choice, per iteration: 128^2 1.99 -> 1.09 us, 512^2 2.03 -> 1.51,
-// 12 x 150 x 203 1.98 -> 1.71, 700^2 2.23 -> 1.99. Choosing by such a model among
-// two and more tiles per CU too was up to 10 % slower than the default (1000 x 1501
-// 293 -> 326 us), so the line is drawn at one.
+// 12 x 150 x 203 1.98 -> 1.71, 700^2 2.23 -> 1.99, 850^2 3.13 -> 2.57. With more
+// tiles per CU the shapes differ by less than the model's error (1000 x 1501 chosen
+// by it: 293 -> 326 us), so the line is drawn there.
 static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
   struct Cost {
-    int waves, rows;
+    int waves, rows, per_cu;
     double fixed, step;
   };
-  static const Cost costs[] = {{8, 8, 6.5, 1.20}, {12, 4, 5.5, 0.92}, {8, 4, 4.7, 0.81}, {16, 4, 7.2, 1.05}};
+  static const Cost costs[] = {{8, 8, 1, 6.5, 1.20}, {12, 4, 1, 5.5, 0.92},  {8, 4, 1, 4.7, 0.81},
+                               {16, 4, 1, 7.2, 1.05}, {12, 4, 2, 12.4, 1.03}, {8, 4, 2, 6.5, 1.10}};
   constexpr int kCus = 256, kMaxT = 14;
   const int images = std::min(batch, kPlainChunk);
   auto per_cu = [&](const Cost& c, int T) {
@@ -141,7 +142,7 @@ static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
   if (m <= 64 && n <= 64) best = (iters + kFlowMaxIters - 1) / kFlowMaxIters * 5.0 + 1.18 * iters;
   for (const Cost& c : costs)
     for (int T = 1; T <= std::min({kMaxT, iters, c.waves * c.rows / 2 - 2}); ++T) {
-      if ((iters + launches(T) - 1) / launches(T) != T || per_cu(c, T) > 1) continue;
+      if ((iters + launches(T) - 1) / launches(T) != T || per_cu(c, T) > c.per_cu) continue;
       const double us = launches(T) * (c.fixed + c.step * T);
       if (us < best) {
         best = us;
