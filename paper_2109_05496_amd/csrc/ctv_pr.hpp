@@ -40,6 +40,8 @@ struct FftArgs {
   const float2* in2;      // kPreExtrapolate: the previous iterate (layout and stride of in)
   float2* zout;           // kPreExtrapolate: where the extrapolated input is stored
   float beta;             // kPreExtrapolate: the momentum weight
+  float* loss_out;        // accumulate-and-invert pass: receives the sum of `partial`, or nullptr
+  int loss_count;         // partials summed
 };
 
 bool fft_size_ok(int v);
@@ -52,6 +54,13 @@ hipError_t launch_transpose(const float2* in, float2* out, int R, int C, int bat
 // epilogue a transpose into tmp (N * W elements per image) and a line pass.
 hipError_t launch_fft_second(FftArgs a, int N, long long W, int dir, int batch, float2* tmp, hipStream_t s);
 int fft_second_blocks(int N, long long W);
+// Along the N-long columns (N >= 32) of one [N][W] image: forward DFT, then for
+// each of `batch` tables H_img (a.H, a.H_stride, [W][N]) the product and the
+// inverse DFT, stored transposed ([W][N], a.img_stride, unscaled). Every image's
+// blocks repeat the forward transform: worth it only where a pass is bound by
+// its latency (fft_spread_pays).
+bool fft_spread_pays(int N, long long W, int batch);
+hipError_t launch_fft_spread(FftArgs a, int N, long long W, int batch, hipStream_t s);
 // Inverse DFT of every N-long column of [N][W] images (N >= 32), the Eq. (27)
 // residual (a.sy, a.sy_stride, a.scale, loss partials in a.partial with
 // fft_second_blocks(N, W) blocks per image), forward DFT back; out keeps the
@@ -59,7 +68,8 @@ int fft_second_blocks(int N, long long W);
 hipError_t launch_fft_roundtrip(FftArgs a, int N, long long W, int batch, hipStream_t s);
 // Along the N-long lines (N >= 32) of the a.n_acc images a.in (stride
 // a.in_stride): out = IDFT(sum_img conj(H_img) (.) a.scale * DFT(line of img)),
-// unscaled, one [lines][N] image (H, H_stride as for kPostAccumulateAll).
+// unscaled, one [lines][N] image (H, H_stride as for kPostAccumulateAll); with
+// loss_out also *loss_out = sum of partial[0 .. loss_count) (as launch_loss_final).
 hipError_t launch_fft_acc_inverse(FftArgs a, int N, long long lines, hipStream_t s);
 hipError_t launch_twiddles(float2* tw, int N, hipStream_t s);
 hipError_t launch_transfer_t(float2* Ht, int m, int n, double dist, double wavelength, double pixel, hipStream_t s);

@@ -413,6 +413,18 @@ __global__ __launch_bounds__(kThreads) void fft_line_kernel(FftArgs a) {
   }
 }
 
+// Sum of partial[i * stride + j] over i < count by one wave: lane l adds the
+// terms l, l + 64, ... in order, then a fixed butterfly combines the lanes,
+// so the summation order (and the result) is the same on every run.
+__device__ __forceinline__ double wave_sum_strided(const double* __restrict__ partial, int count,
+                                                   long long stride, int j) {
+  double s = 0.0;
+  for (int i = (int)threadIdx.x; i < count; i += 64) s += partial[(long long)i * stride + j];
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
+  return s;
+}
+
 // Along the lines of [lines][N] images (the m-direction of the transposed
 // spectrum layout, N >= 32): the forward DFT of a line of each of the n_acc
 // images, scaled by a.scale and multiplied by conj(H_img) at the same
@@ -439,6 +451,15 @@ __global__ __launch_bounds__(kThreads) void fft_acc_inverse_kernel(FftArgs a) {
   constexpr int LS = N + N / 16;
   __shared__ float2 s[SLOTS * LS];
   __shared__ float2 twh[N / 2];
+  if (a.loss_out && blockIdx.x == gridDim.x - 1) {
+    // one extra block sums the loss partials of the previous pass beside the
+    // transforms (a launch of its own took 1.8 - 4.6 us per outer iteration)
+    if (threadIdx.x < 64) {
+      const double t = wave_sum_strided(a.partial, a.loss_count, 1, 0);
+      if (threadIdx.x == 0) *a.loss_out = (float)t;
+    }
+    return;
+  }
   const int slot = threadIdx.x / TPL;
   const int g = slot % G, li = slot / G;
   const int lt = threadIdx.x % TPL;
@@ -634,6 +655,54 @@ __global__ __launch_bounds__(CB * (N / E)) void fft_col_kernel(FftArgs a) {
   }
 }
 
+// The column pass of a forward transform and the first pass of the inverse
+// transforms of its products with H_img in one: the columns of an [N][W] image
+// staged through LDS, forward DFT along them, times H_img, inverse DFT along
+// the same direction, stored as lines of [W][N]. Block row y takes table y and
+// repeats the forward transform. Bound by the latency of one column (load, two
+// transforms, store), which is why it replaces two launches for small problems:
+// 256^2 with one distance 8.9 us for the two passes, 5.4 us here.
+template <int N, int CB, int E>
+__global__ __launch_bounds__(CB * (N / E)) void fft_col_spread_kernel(FftArgs a) {
+  constexpr int TPL = N / E;
+  constexpr int NT = CB * TPL;
+  constexpr int LS = N + N / 16 + 4;  // as in fft_col_kernel
+  __shared__ float2 s[CB * LS];
+  __shared__ float2 twh[N / 2];
+  const long long W = a.lines;
+  const int cl = threadIdx.x / TPL;
+  const int lt = threadIdx.x % TPL;
+  const int grp = xcd_remap(blockIdx.x, gridDim.x);
+  const long long col = (long long)grp * CB + cl;
+  const bool live = col < W;
+  float2* sl = s + cl * LS;
+  const int img = blockIdx.y;
+  TwStage<N, NT> tws;
+  tws.fetch(a.tw);
+  const float2* H = a.H + (long long)img * a.H_stride + (live ? col : 0) * N + lt;
+  float2 h[16];
+#pragma unroll
+  for (int r = 0; r < E; ++r) h[r] = H[r * TPL];
+  stage_columns<N, CB, NT, LS, E>(a.in, (int)W, grp, s);
+  tws.store(twh);
+  float2 o[16], v[16];
+  int pos[16];
+  line_from_lds<N, E>(sl, v);
+  line_fft_regs<N, -1, false, E>(sl, twh, v, o, pos);
+  __syncthreads();  // every thread's last forward pass has read its line
+#pragma unroll
+  for (int r = 0; r < E; ++r) sl[pidx(pos[r])] = o[r];
+  __syncthreads();
+#pragma unroll
+  for (int r = 0; r < E; ++r) v[r] = cmul(sl[pidx(lt + r * TPL)], h[r]);
+  line_fft_regs<N, 1, true, E>(sl, twh, v, o, pos);
+  if (live) {
+    float2* out = a.out + (long long)img * a.img_stride + col * N;
+#pragma unroll
+    for (int r = 0; r < E; ++r) out[pos[r]] = o[r];
+  }
+}
+
 // Round trip along the columns of an [N][W] image (the transposed spectrum
 // layout: N = n, W = m), for the gradient of Eq. (27): the inverse DFT of every
 // column (which completes A_d x, the m-direction having been inverted by the
@@ -773,18 +842,6 @@ __global__ __launch_bounds__(256) void sqrt_y_kernel(const float* __restrict__ y
   const float v = sqrtf(fmaxf(y[p], 0.0f));
   sy[p] = v;
   if (syc) syc[p] = make_float2(v, 0.0f);
-}
-
-// Sum of partial[i * stride + j] over i < count by one wave: lane l adds the
-// terms l, l + 64, ... in order, then a fixed butterfly combines the lanes,
-// so the summation order (and the result) is the same on every run.
-__device__ __forceinline__ double wave_sum_strided(const double* __restrict__ partial, int count,
-                                                   long long stride, int j) {
-  double s = 0.0;
-  for (int i = (int)threadIdx.x; i < count; i += 64) s += partial[(long long)i * stride + j];
-#pragma unroll
-  for (int off = 32; off > 0; off >>= 1) s += __shfl_xor(s, off, 64);
-  return s;
 }
 
 __global__ __launch_bounds__(64) void loss_final_kernel(const double* __restrict__ partial, int count,
@@ -972,6 +1029,40 @@ hipError_t launch_fft_second(FftArgs a, int N, long long W, int dir, int batch, 
   return dir < 0 ? launch_col_dir<-1>(a, N, batch, s) : launch_col_dir<1>(a, N, batch, s);
 }
 
+// Worth it below 2^18 elements over all images, where two passes cost twice the
+// latency of one, and for a single image (nothing is repeated) as long as both
+// passes it replaces run the same elements per thread (fft_few_waves), so that
+// the result is theirs bit for bit.
+bool fft_spread_pays(int N, long long W, int batch) {
+  const long long total = W * (long long)N * batch;
+  return N >= 32 && (total <= (1LL << 18) || (batch == 1 && total < (1LL << 21)));
+}
+
+hipError_t launch_fft_spread(FftArgs a, int N, long long W, int batch, hipStream_t s) {
+  if (!fft_spread_pays(N, W, batch)) return hipErrorInvalidValue;  // also keeps offsets within 32 bits
+  a.lines = W;
+  const bool narrow = (W + 7) / 8 * batch < 256;
+#define CTV_SPK(NN)                                                                                     \
+  case NN: {                                                                                            \
+    constexpr int e = NN >= 256 && NN <= 2048 ? 8 : 16;                                                 \
+    constexpr int cb = col_block<NN>();                                                                 \
+    constexpr int cbn = cb == 8 && NN >= 256 ? 4 : cb;                                                  \
+    const int c = narrow ? cbn : cb;                                                                    \
+    const dim3 grid((unsigned)((W + c - 1) / c), (unsigned)batch);                                      \
+    if (narrow)                                                                                         \
+      hipLaunchKernelGGL((fft_col_spread_kernel<NN, cbn, e>), grid, dim3(cbn * (NN / e)), 0, s, a);     \
+    else                                                                                                \
+      hipLaunchKernelGGL((fft_col_spread_kernel<NN, cb, e>), grid, dim3(cb * (NN / e)), 0, s, a);       \
+    break;                                                                                              \
+  }
+  switch (N) {
+    CTV_SPK(32) CTV_SPK(64) CTV_SPK(128) CTV_SPK(256) CTV_SPK(512) CTV_SPK(1024) CTV_SPK(2048) CTV_SPK(4096)
+    default: return hipErrorInvalidValue;
+  }
+#undef CTV_SPK
+  return hipGetLastError();
+}
+
 hipError_t launch_fft_roundtrip(FftArgs a, int N, long long W, int batch, hipStream_t s) {
   if ((long long)N * W > INT_MAX) return hipErrorInvalidValue;  // 32-bit offsets within an image
   a.lines = W;
@@ -995,7 +1086,7 @@ hipError_t launch_fft_acc_inverse(FftArgs a, int N, long long lines, hipStream_t
 #define CTV_AIK(NN)                                                                     \
   case NN: {                                                                            \
     constexpr int lpb = acc_lines_per_block<NN>();                                      \
-    const dim3 grid((unsigned)((lines + lpb - 1) / lpb));                               \
+    const dim3 grid((unsigned)((lines + lpb - 1) / lpb + (a.loss_out ? 1 : 0)));        \
     if (a.n_acc <= acc_groups<NN>())                                                    \
       hipLaunchKernelGGL((fft_acc_inverse_kernel<NN, true>), grid, dim3(kThreads), 0, s, a); \
     else                                                                                \

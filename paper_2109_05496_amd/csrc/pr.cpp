@@ -118,9 +118,6 @@ FftArgs line_args(const float2* in, float2* out, const float2* tw, long long str
   return a;
 }
 
-// Spectrum (transposed, [n][m]) of a natural-layout [m][n] image: a pass along
-// n, then a column pass along m that writes the transposed layout, with
-// epilogue `last` (in/out/tw filled here).
 // The momentum step of Algorithm 1 (line 5) done in the first pass of the
 // next transform: z = x + beta (x - x_prev), stored to z on the way.
 struct Extrapolate {
@@ -129,10 +126,9 @@ struct Extrapolate {
   float2* z;
 };
 
-ctv_status fft2_to_t(const Ctx& c, const float2* in, float2* out, FftArgs last, const Extrapolate* ex = nullptr) {
-  float2* t1 = c.at(c.L.t1);
-  float2* t2 = c.at(c.L.t2);
-  FftArgs a = line_args(in, t1, c.at(c.L.tw_n), c.px);
+// The pass along n of a natural-layout [m][n] image, same layout.
+ctv_status fft_rows(const Ctx& c, const float2* in, float2* out, const Extrapolate* ex) {
+  FftArgs a = line_args(in, out, c.at(c.L.tw_n), c.px);
   if (ex) {
     a.pre = kPreExtrapolate;
     a.in2 = ex->x_prev;
@@ -140,6 +136,17 @@ ctv_status fft2_to_t(const Ctx& c, const float2* in, float2* out, FftArgs last, 
     a.zout = ex->z;
   }
   CTV_TRY(launch_fft_lines(a, c.n, c.m, -1, 1, c.s), "fft (rows)");
+  return CTV_OK;
+}
+
+// Spectrum (transposed, [n][m]) of a natural-layout [m][n] image: a pass along
+// n, then a column pass along m that writes the transposed layout, with
+// epilogue `last` (in/out/tw filled here).
+ctv_status fft2_to_t(const Ctx& c, const float2* in, float2* out, FftArgs last, const Extrapolate* ex = nullptr) {
+  float2* t1 = c.at(c.L.t1);
+  float2* t2 = c.at(c.L.t2);
+  ctv_status st = fft_rows(c, in, t1, ex);
+  if (st) return st;
   last.in = t1;
   last.out = out;
   last.tw = c.at(c.L.tw_m);
@@ -218,17 +225,28 @@ ctv_status gradient(const Ctx& c, const float2* z, float2* out, bool post_step, 
   float2* acc = c.at(c.L.acc);
   double* part = reinterpret_cast<double*>(c.ws + c.L.part);
   const int rb = residual_blocks(c.m, c.n);
-  ctv_status st = fft2_to_t(c, z, xh, epilogue(kPostStore, 1.0f), ex);
-  if (st) return st;
-  if (ex) z = ex->z;
   // A_d z = IFFT2(H_d Z) for all d (one shared input spectrum), then the
-  // residual bracket of Eq. (27) in t2[d]
-  FftArgs a = line_args(xh, t1, c.at(c.L.tw_m), c.px);
-  a.in_stride = 0;
-  a.pre = kPreMulH;
-  a.H = c.Ht(0);
-  a.H_stride = c.px;
-  CTV_TRY(launch_fft_lines(a, c.m, c.n, 1, c.D, c.s), "ifft (columns)");
+  // residual bracket of Eq. (27) in t2[d]: along n, then along m forward, times
+  // H_d and inverse (one pass for small problems, else through the spectrum xh)
+  ctv_status st;
+  if (fft_spread_pays(c.m, c.n, c.D)) {
+    st = fft_rows(c, z, xh, ex);
+    if (st) return st;
+    FftArgs a = line_args(xh, t1, c.at(c.L.tw_m), c.px);
+    a.H = c.Ht(0);
+    a.H_stride = c.px;
+    CTV_TRY(launch_fft_spread(a, c.m, c.n, c.D, c.s), "fft (columns) and back");
+  } else {
+    st = fft2_to_t(c, z, xh, epilogue(kPostStore, 1.0f), ex);
+    if (st) return st;
+    FftArgs a = line_args(xh, t1, c.at(c.L.tw_m), c.px);
+    a.in_stride = 0;
+    a.pre = kPreMulH;
+    a.H = c.Ht(0);
+    a.H_stride = c.px;
+    CTV_TRY(launch_fft_lines(a, c.m, c.n, 1, c.D, c.s), "ifft (columns)");
+  }
+  if (ex) z = ex->z;
   if (c.n >= 32) {
     // along n: inverse, residual, forward again in one pass (t1 -> t2, [n][m]);
     // then the forward pass along m with acc = sum_d conj(H_d) (.) over the distances
@@ -245,6 +263,9 @@ ctv_status gradient(const Ctx& c, const float2* z, float2* out, bool post_step, 
       q.H = c.Ht(0);
       q.H_stride = c.px;
       q.n_acc = c.D;
+      q.partial = part;
+      q.loss_out = loss;
+      q.loss_count = c.D * rb;
       CTV_TRY(launch_fft_acc_inverse(q, c.m, c.n, c.s), "fft (columns, accumulate, inverse)");
       FftArgs g = epilogue(post_step ? kPostStep : kPostStore, inv);
       g.z = z;
@@ -254,7 +275,6 @@ ctv_status gradient(const Ctx& c, const float2* z, float2* out, bool post_step, 
       g.tw = c.at(c.L.tw_n);
       g.in_stride = g.img_stride = c.px;
       CTV_TRY(launch_fft_second(g, c.n, c.m, 1, 1, t2, c.s), "ifft (rows)");
-      if (loss) CTV_TRY(launch_loss_final(part, c.D * rb, loss, c.s), "loss");
       return CTV_OK;
     }
     FftArgs q = line_args(t2, nullptr, c.at(c.L.tw_m), c.px);
