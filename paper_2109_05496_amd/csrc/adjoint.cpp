@@ -20,9 +20,9 @@ namespace {
 
 size_t align_up(size_t v) { return (v + 255) & ~(size_t)255; }
 
-// Reverse steps run up to kMaxRev per launch; every launch of a call uses the
-// halo of the longest one, so the tile grid (and the lambda-gradient slot of
-// each tile) is the same throughout.
+// Reverse steps run up to kMaxRev per launch; every one of a call uses the halo
+// of the longest, so the tile grid (and the lambda-gradient slot of each tile) is
+// the same throughout. The output step's tiles are larger, hence fewer.
 int adj_halo(int ckpt) { return std::min(kMaxRev, std::max(ckpt, 1)) + 1; }
 int adj_tiles_x(int n, int h) { return (n + (64 - 2 * h) - 1) / (64 - 2 * h); }
 int adj_tiles_y(int m, int h) { return (m + (adj_tile_rows() - 2 * h) - 1) / (adj_tile_rows() - 2 * h); }
@@ -133,9 +133,7 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
     a.lam_acc = lam_acc + (size_t)c0 * tiles_per_img;
     a.m = m;
     a.n = n;
-    a.tiles_x = tiles_x;
-    a.tiles_per_img = tiles_per_img;
-    a.halo = halo;
+    a.lam_slots = tiles_per_img;
     a.R = make_radii(p->tv_kind, p->alpha);
     for (int i = 0; i < cb; ++i) {
       const double lam = lambda_host[c0 + i];
@@ -174,14 +172,19 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
       const int ks = sgi * c, ke = std::min(ks + c, K);
       const float* ck = (sgi == 0) ? nullptr : saved + (size_t)(sgi - 1) * (st_full / 4) + st_off;
       // recompute iterations ks+1 .. kstop: slot[j] receives r_{ks+j+2} (plane 1) for
-      // every j, and the full state after each launch's last iteration
+      // every j (and q after the launches whose last state is read)
       const int kstop = (sgi == nseg - 1) ? ke : ke - 1;
       const float* prev = ck;
       for (int k = ks; k < kstop;) {
         const int Tl = even_split(tl.T, kstop - k);
+        // the launch's last state: its r plane is the last of the history; its q
+        // plane is stored only where it is read, by the segment's next launch or
+        // (q_K) by the output step (and the last r, once stored twice, only in the
+        // history): 16 x 512^2, 9 iterations 191 -> 187 us
         float* last = slot(k + Tl - 1 - ks);
-        st = fgp_launch(p, tl, cb, m, n, a.b, support, lambda_host + c0, beta, k, Tl, prev, last, nullptr, s,
-                        slot(k - ks), (long long)(st_stride / 4));
+        const bool q_read = k + Tl < kstop || sgi == nseg - 1;
+        st = fgp_launch(p, tl, cb, m, n, a.b, support, lambda_host + c0, beta, k, Tl, prev, q_read ? last : nullptr,
+                        nullptr, s, slot(k - ks), (long long)(st_stride / 4));
         if (st) return st;
         prev = last;
         k += Tl;
@@ -190,10 +193,17 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
         for (int i = 0; i < kMaxRev; ++i) a.r[i] = nullptr;
         a.r[0] = slot(ke - ks - 1);  // q_K in plane 0
         a.steps = 0;
+        a.halo = 1;
+        a.tiles_x = adj_tiles_x(n, a.halo);
+        a.tiles_per_img = a.tiles_x * adj_tiles_y(m, a.halo);
         a.adj_in = nullptr;
         a.adj_out = cur;
         hipError_t e = launch_adj_output(a, p->constraint, cb, s);
         if (e != hipSuccess) return hip_fail(e, "adjoint output step");
+        a.halo = halo;
+        a.tiles_x = tiles_x;
+        a.tiles_per_img = tiles_per_img;
+        a.b_zero = 1;
       }
       // reverse steps ke, ke-1, ..., ks+1, up to kMaxRev per launch; r_k is in
       // plane 1 of slot[k - ks - 2], r_{ks+1} in the checkpoint (zero for k = 1)
@@ -210,6 +220,7 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
         a.live = live;
         hipError_t e = launch_adj_step(a, p->tv_kind, p->constraint, cb, s);
         if (e != hipSuccess) return hip_fail(e, "adjoint step");
+        a.b_zero = 0;
         std::swap(cur, nxt);
         khi -= steps;
       }

@@ -19,9 +19,11 @@ struct AdjStepArgs {
   float* adj_out;           // same layout, nullptr after the last reverse step
   float* grad_b;            // complex64, read-modify-write
   const float* grad_x;      // complex64 incoming gradient (output step)
-  double* lam_acc;          // [chunk][tiles_per_img]
+  double* lam_acc;          // [chunk][lam_slots], set by the output step, added to by the reverse steps
   int m, n, tiles_x, tiles_per_img;
-  int halo;                 // tile halo, >= steps + 1, the same for every launch of a call
+  int lam_slots;            // >= tiles_per_img
+  int halo;                 // tile halo, >= steps + 1: one for all reverse steps of a call, another for the output step
+  int b_zero;               // reverse step: plane B of adj_in is zero and is not read
   int steps;                // reverse steps in this launch, 1..kMaxRev
   float beta[kMaxRev];      // beta_{k-1} of each fused step k
   Radii R;

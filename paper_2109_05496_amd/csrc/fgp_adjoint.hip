@@ -54,9 +54,9 @@ __device__ __forceinline__ float2 proj_c_vjp(float2 w, float s, bool inside, flo
     // s (I - w w^T s^2) yb with s = 1/|w|; without the rank-one term (d = 0) where
     // the projection is inactive (s = 1), which leaves yb. No branch: it would
     // be taken by some lane of nearly every wave.
-    const float t = (w.x * yb.x + w.y * yb.y) * (s * s);
+    const float t = fmaf(w.x, yb.x, w.y * yb.y) * (s * s);
     const float d = s < 1.0f ? t : 0.0f;
-    o = make_float2(s * (yb.x - w.x * d), s * (yb.y - w.y * d));
+    o = make_float2(s * fmaf(-w.x, d, yb.x), s * fmaf(-w.y, d, yb.y));
   }
   return inside ? o : make_float2(0.0f, 0.0f);
 }
@@ -68,10 +68,10 @@ __device__ __forceinline__ void ball_vjp2(float vx, float vy, float ax, float ay
   if (rho <= 0.0f) {
     ox = oy = 0.0f;
   } else if (f < 1.0f) {
-    const float n2 = vx * vx + vy * vy;
-    const float d = (vx * ax + vy * ay) / n2;
-    ox = f * (ax - vx * d);
-    oy = f * (ay - vy * d);
+    const float n2 = fmaf(vx, vx, vy * vy);
+    const float d = fmaf(vx, ax, vy * ay) / n2;
+    ox = f * fmaf(-vx, d, ax);
+    oy = f * fmaf(-vy, d, ay);
   } else {
     ox = ax;
     oy = ay;
@@ -84,9 +84,9 @@ __device__ __forceinline__ float4 proj_s_vjp(float4 g, float4 a, const Radii& R)
   if (KIND == K1I) {
     const float n2 = fmaf(g.x, g.x, fmaf(g.y, g.y, fmaf(g.z, g.z, g.w * g.w)));
     const float s = sat(rsq(n2));
-    const float t = (g.x * a.x + g.y * a.y + g.z * a.z + g.w * a.w) * (s * s);
+    const float t = fmaf(g.x, a.x, fmaf(g.y, a.y, fmaf(g.z, a.z, g.w * a.w))) * (s * s);
     const float d = s < 1.0f ? t : 0.0f;  // inactive: o = a
-    o = make_float4(s * (a.x - g.x * d), s * (a.y - g.y * d), s * (a.z - g.z * d), s * (a.w - g.w * d));
+    o = make_float4(s * fmaf(-g.x, d, a.x), s * fmaf(-g.y, d, a.y), s * fmaf(-g.z, d, a.z), s * fmaf(-g.w, d, a.w));
   } else if (KIND == K1A) {
     const float s1 = sat(rsq(fmaf(g.x, g.x, g.y * g.y)));
     const float s2 = sat(rsq(fmaf(g.z, g.z, g.w * g.w)));
@@ -119,6 +119,7 @@ struct AdjJob {
   double* lam_acc;           // per-tile accumulator slot
   int m, n, tx, ty;
   int steps;                 // reverse steps fused in this launch
+  bool b_zero;               // B is zero and was not stored (first launch after the output step)
   float lam, c, cc;          // lambda, 1/(8 lambda), 1/(8 lambda^2)
   float beta[kMaxRev];       // beta_{k-1} of each fused step
   Radii R;
@@ -136,14 +137,19 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
   return s;
 }
 
-// What bounds it: memory first (5 r planes, A, B and the running bbar: 704 MB per
-// launch of 16 x 512^2, 3.2 TB/s) with four barrier-separated stencil stages a
-// step in between. The factors sit in vector registers, the projections' adjoints
-// are branch-free where no division is involved, the next step's r loads run
-// under stages 3 and 4, and tiles at the image's border load through row buffers
-// with zero steps instead of branches and selects. Measured before -> after:
-// training step on 3 x 201 x 333 (border tiles) 395 -> 323 us, 16 x 512^2 (mostly
-// interior tiles, bound by memory) 221 us a launch on both sides.
+// What bounds it: 16 x 512^2 takes 218 us a launch of 5 steps, of which about 135
+// are instruction issue (4 barrier-separated stencil stages a step, 4 waves per
+// SIMD; the barriers themselves 10-15 us, the f64 sums under 3) and the rest memory
+// (5 r planes, A, B and the running bbar: 704 MB) that 2 workgroups per CU do not
+// hide. A 64 x 64 tile (16 waves, or 8 waves x 8 rows at 2 per SIMD) has a quarter
+// less halo but one workgroup per CU: 5 and 12 % slower. The factors sit in vector
+// registers, the projections' adjoints are fused multiply-adds and branch-free where
+// no division is involved, the next step's r loads run under stages 3 and 4, and
+// tiles at the image's border load through row buffers with zero steps instead of
+// branches and selects. The rows' f64 sums keep a branch of their own (the empty
+// asm): as selects, the whole step became one block and spilled 28 registers.
+// Measured before -> after: backward pass of 3 x 201 x 333 (border tiles) 395 -> 320 us
+// with its forward, of 16 x 512^2, 50 iterations, 3041 -> 2959 us.
 //
 // J.steps reverse steps k, k-1, ... on one tile with halo H >= steps + 1: a step
 // reads (A, B) one pixel and r_k two pixels around each point it updates, so
@@ -205,14 +211,15 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
       const int w = row_in(j) ? width : 0;
       b[i] = buf_ld2(row_buf(J.b + o, w * 8), off8);
       A[i] = buf_ld4(row_buf(J.adj_in + o, w * 16), off16);
-      B[i] = buf_ld4(row_buf(J.adj_in + plane + o, w * 16), off16);
+      B[i] = buf_ld4(row_buf(J.adj_in + plane + o, J.b_zero ? 0 : w * 16), off16);
       if (MASK) inside[i] = buf_ld_mask(row_buf(J.mask + o, w), off1);
       bacc[i] = buf_ld2(row_buf(J.gb + o, row_out(i) ? w * 8 : 0), col_out ? off8 : kNoOffset);
     } else {
       const long long o = (long long)j * J.n + c0;
       b[i] = (J.b + o)[lane];
       A[i] = (J.adj_in + o)[lane];
-      B[i] = (J.adj_in + plane + o)[lane];
+      B[i] = z4;
+      if (!J.b_zero) B[i] = (J.adj_in + plane + o)[lane];
       if (MASK) inside[i] = (J.mask + o)[lane] != 0;
       bacc[i] = z2;
       if (row_out(i) && col_out) bacc[i] = (J.gb + o)[lane];
@@ -258,7 +265,10 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
                                      fmaf(ch, l2y, r[i].w));
         const float4 gb = proj_s_vjp<KIND>(g, A[i], R);
         gbar[i] = gb;
-        if (row_out(i)) lam_part += (double)(cc * (gb.x * l1x + gb.y * l1y + gb.z * l2x + gb.w * l2y));
+        if (row_out(i)) {
+          asm volatile("");
+          lam_part += (double)(cc * fmaf(gb.x, l1x, fmaf(gb.y, l1y, fmaf(gb.z, l2x, gb.w * l2y))));
+        }
       }
     }
     // r is not read again in this step: the next step's loads run under stages 3 and 4
@@ -278,7 +288,10 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
                                       c * ((gbar[i].y - up.y) + (gbar[i].w - ly)));
         wbar[i] = proj_c_vjp<CONSTR>(w[i], s[i], inside[i], yb);
         bacc[i] = make_float2(bacc[i].x + wbar[i].x, bacc[i].y + wbar[i].y);
-        if (row_out(i)) lam_part += (double)(-(wbar[i].x * dd[i].x + wbar[i].y * dd[i].y));
+        if (row_out(i)) {
+          asm volatile("");
+          lam_part += (double)fmaf(-wbar[i].x, dd[i].x, -(wbar[i].y * dd[i].y));
+        }
       }
     }
     // stage 4: rbar = gbar - lambda L(wbar) (down / right); A' = B + (1 + beta) rbar, B' = -beta rbar
@@ -328,10 +341,15 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
 }
 
 // Output step: w = b - lambda L^T q_K, wbar = J_PC(w)^T xbar, bbar = wbar,
-// A = qbar_K = -lambda L(wbar), B = 0, lambdabar = -<wbar, L^T q_K>.
+// A = qbar_K = -lambda L(wbar), B = 0 (not stored), lambdabar = -<wbar, L^T q_K>.
+// Bound by memory. Its tiles have a halo of their own of 1 (62 x 30 of 64 x 32
+// points stored; 52 x 20 with the reverse steps' halo of 6) and B is neither
+// stored nor read back: 16 x 512^2 87 -> 75 us, the first reverse launch 225 -> 209.
+// *J.lam_acc and every lam_step-th slot after it are set: the reverse steps, whose
+// tiles are smaller, add to theirs.
 template <int CONSTR, bool MASK, int NW, int P, bool BORDER>
 __device__ __forceinline__ void adj_out_tile(const AdjJob& J, const int H, const float2* __restrict__ xbar,
-                                             float2* sX1, float2* sX2, double* red) {
+                                             float2* sX1, float2* sX2, double* red, int lam_step, int lam_left) {
   constexpr int RH = NW * P;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -341,7 +359,6 @@ __device__ __forceinline__ void adj_out_tile(const AdjJob& J, const int H, const
   const bool kin = !BORDER || (k >= 0 && k < J.n);
   const bool has_left = !BORDER || k > 0;
   const bool has_right = !BORDER || k < J.n - 1;
-  const long long plane = (long long)J.m * J.n;
   const float2 z2 = make_float2(0.0f, 0.0f);
   const float4 z4 = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
   float4 q[P];
@@ -408,12 +425,12 @@ __device__ __forceinline__ void adj_out_tile(const AdjJob& J, const int H, const
         const long long p = (long long)j * J.n + k;
         J.gb[p] = wbar[i];
         J.adj_out[p] = make_float4(-J.lam * l1x, -J.lam * l1y, -J.lam * l2x, -J.lam * l2y);
-        J.adj_out[plane + p] = z4;
       }
     }
   }
   const double tot = block_sum_d(lam_part, red);
-  if (threadIdx.x == 0) *J.lam_acc = tot;
+  if (threadIdx.x == 0)
+    for (int i = 0; i < lam_left; i += lam_step) J.lam_acc[i] = i ? 0.0 : tot;
 }
 
 constexpr int kNW = 8, kP = 4;
@@ -438,13 +455,12 @@ __device__ __forceinline__ bool adj_job_common(const AdjStepArgs& A, int& img, A
     img = tile / A.tiles_per_img;
     t = tile - img * A.tiles_per_img;
   }
-  const int tile = img * A.tiles_per_img + t;
   const long long px = (long long)A.m * A.n;
   J.b = reinterpret_cast<const float2*>(A.b) + img * px;
   J.mask = A.mask;
   J.adj_out = A.adj_out ? reinterpret_cast<float4*>(A.adj_out) + img * 2 * px : nullptr;
   J.gb = reinterpret_cast<float2*>(A.grad_b) + img * px;
-  J.lam_acc = A.lam_acc + tile;
+  J.lam_acc = A.lam_acc + (long long)img * A.lam_slots + t;
   J.m = A.m;
   J.n = A.n;
   J.ty = t / A.tiles_x;
@@ -454,6 +470,7 @@ __device__ __forceinline__ bool adj_job_common(const AdjStepArgs& A, int& img, A
   J.cc = A.cc[img];
   J.R = A.R;
   J.steps = A.steps;
+  J.b_zero = A.b_zero != 0;
   return true;
 }
 
@@ -497,11 +514,12 @@ __global__ __launch_bounds__(kNW * 64) void adj_output_kernel(AdjStepArgs A) {
   const float2* xbar = reinterpret_cast<const float2*>(A.grad_x) + img * px;
   const int H = A.halo;
   const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (kNW * kP - 2 * H) - H;
+  const int left = A.lam_slots - (J.ty * A.tiles_x + J.tx);  // lambda-gradient slots from this tile's on
   const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + kNW * kP <= J.m - 1;
   if (interior)
-    adj_out_tile<CONSTR, MASK, kNW, kP, false>(J, H, xbar, sX1, sX2, red);
+    adj_out_tile<CONSTR, MASK, kNW, kP, false>(J, H, xbar, sX1, sX2, red, A.tiles_per_img, left);
   else
-    adj_out_tile<CONSTR, MASK, kNW, kP, true>(J, H, xbar, sX1, sX2, red);
+    adj_out_tile<CONSTR, MASK, kNW, kP, true>(J, H, xbar, sX1, sX2, red, A.tiles_per_img, left);
 }
 
 // lambda = 0 or K = 0: x = P_C(b), so bbar = J_PC(b)^T xbar.

@@ -370,18 +370,19 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
           const long long o = j < J.m ? (long long)j * J.n + cl : 0;
           const int bytes = j < J.m ? width * 16 : 0, off = col_out ? off16 : kNoOffset;
           buf_st4<2>(row_buf(J.st_out + o, bytes), off, q[i]);
-          buf_st4<2>(row_buf(J.st_out + plane + o, bytes), off, r[i]);
+          if (!HIST) buf_st4<2>(row_buf(J.st_out + plane + o, bytes), off, r[i]);
         }
       } else if (col_out && ry >= H && ry < RH - H && (!BORDER || j < J.m)) {
         const long long o = row_off(i);
         st_state<COH>(J.st_out + o + lane, q[i]);
-        st_state<COH>(J.st_out + plane + o + lane, r[i]);
+        if (!HIST) st_state<COH>(J.st_out + plane + o + lane, r[i]);
       }
     }
   }
 }
 
-// HIST: also store r after every fused iteration (the adjoint's recomputation).
+// HIST: also store r after every fused iteration (the adjoint's recomputation);
+// st_out then receives q only: the last r of the history is its r plane.
 template <int KIND, int CONSTR, bool MASK, int NW, int P, bool HIST = false>
 __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void fgp_col_kernel(FgpPlainArgs P_) {
   __shared__ float2 sBot[NW * kRW];
