@@ -69,10 +69,12 @@ __device__ __forceinline__ void buf_st2(__amdgpu_buffer_rsrc_t r, int off, float
   __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, AUX);
 }
 
-// Bits [max(a, 0), min(b, n)) set: the rows i of a wave with a <= i < b.
+// Bits [max(a, 0), min(b, n)) set: the rows i of a wave with a <= i < b. a and b
+// are the same in every lane; readfirstlane between the two bounds
+// keeps them scalar (the compiler makes a vector median of them otherwise).
 __device__ __forceinline__ unsigned row_bits(int a, int b, int n) {
-  a = min(max(a, 0), n);
-  b = min(max(b, 0), n);
+  a = min(__builtin_amdgcn_readfirstlane(max(a, 0)), n);
+  b = min(__builtin_amdgcn_readfirstlane(max(b, 0)), n);
   return ((1u << b) - 1u) & ~((1u << a) - 1u);
 }
 

@@ -169,6 +169,13 @@ __device__ __forceinline__ void st_state(float4* p, float4 v) {
   __hip_atomic_store(u + 1, b, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
 }
 
+// Occupancy of a tile shape. A wave of 4 rows needs 63-67 registers, one of 8 rows
+// 115-120: two 16-wave tiles share a CU only at 64, i.e. 8 waves per SIMD, which
+// hide the barriers and the latencies of the row chains that 4 waves leave open.
+// 64 x 64 region, 8 iterations a launch, 16 x 4 against 8 x 8 at 4 waves: 2048^2 x 80
+// 793 -> 746 us (1i), 839 -> 775 (1a), 845 -> 791 (2i), 779 -> 722 (2a), 8192^2
+// 11.65 -> 11.27 ms. The other 4-row shapes fill their SIMDs at 66.
+constexpr int waves_per_simd(int NW, int P) { return NW == 16 && P == 4 ? 8 : 4; }
 
 // BORDER = false is the path for tiles whose region lies at least one pixel
 // inside the image on every side: no neighbour there leaves the image. BORDER =
@@ -184,7 +191,7 @@ __device__ __forceinline__ void st_state(float4* p, float4 v) {
 // of the fused iterations); one row more than the q rows needs y.
 template <int KIND, int CONSTR, bool MASK, int NW, int P, bool BORDER, bool HIST = false, bool COH = false>
 __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, const float* sBeta,
-                                             float2* __restrict__ sBot, float2* __restrict__ sTop) {
+                                             float2* __restrict__ sRows) {
   constexpr int RH = NW * P;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -205,10 +212,22 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
   // wave, so each access below is a scalar row base plus the lane's offset
   // (no per-lane 64-bit address arithmetic).
   auto row_off = [&](int i) { return (long long)(jb + i) * J.n + c0; };
+  // Rows handed between waves: NW + 1 last rows of r (the wave above's at sw[0],
+  // this wave's at sw[kRW]), then NW + 1 first rows of y (this wave's at sw[kTop],
+  // the wave below's one row on). One address register with constant offsets; the
+  // rows above the first and below the last wave are zero.
+  constexpr int kTop = (NW + 1) * kRW;
+  float2* const sw = sRows + wave * kRW + lane;
+  if (wave == 0) sw[0] = zero2;
+  if (wave == NW - 1) sw[kTop + kRW] = zero2;
   const float lam = in_vgpr(J.lam), c = in_vgpr(J.c);
   Radii R = J.R;
-  R.ra = in_vgpr(R.ra);
-  R.sa = in_vgpr(R.sa);
+  // in scalar registers for type 2a, which clips to them at half rate with any
+  // operand, and where 64 registers are the limit
+  if (KIND != K2A && waves_per_simd(NW, P) < 8) {
+    R.ra = in_vgpr(R.ra);
+    R.sa = in_vgpr(R.sa);
+  }
   // Steps of the vertical and horizontal differences: 0 where the lower / right
   // neighbour lies outside the image (and outside the image itself), which
   // keeps the duals that do not exist at exactly 0 without a select, so a
@@ -294,10 +313,9 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
     // Live rows of this wave as bit masks (uniform): y on [lo, hi], q on [lo, hi).
     const int lo = it + 1 + eu - wave * P, hi = RH - (it + 1) - ed - wave * P;
     const unsigned ym = row_bits(lo, hi + 1, P), qm = row_bits(lo, hi, P);
-    sBot[wave * kRW + lane] = make_float2(r[P - 1].x, r[P - 1].y);
+    sw[kRW] = make_float2(r[P - 1].x, r[P - 1].y);
     __syncthreads();
-    const float2 up_lds = sBot[(wave > 0 ? wave - 1 : 0) * kRW + lane];
-    const float2 up0 = (wave > 0) ? up_lds : zero2;
+    const float2 up0 = sw[0];
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       if (ym & (1u << i)) {
@@ -306,10 +324,9 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
         y[i] = proj_c<CONSTR>(dual_to_primal(b[i], r[i], up, make_float2(lx, ly), lam), inside[i]);
       }
     }
-    sTop[wave * kRW + lane] = y[0];
+    sw[kTop] = y[0];
     __syncthreads();
-    const float2 down_lds = sTop[(wave < NW - 1 ? wave + 1 : wave) * kRW + lane];
-    const float2 down_last = (wave < NW - 1) ? down_lds : y[P - 1];
+    const float2 down_last = sw[kTop + kRW];
     const float beta = sBeta[it];
 #pragma unroll
     for (int i = 0; i < P; ++i) {
@@ -340,10 +357,9 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
   }
 
   if (J.x) {
-    sBot[wave * kRW + lane] = make_float2(q[P - 1].x, q[P - 1].y);
+    sw[kRW] = make_float2(q[P - 1].x, q[P - 1].y);
     __syncthreads();
-    const float2 up_lds = sBot[(wave > 0 ? wave - 1 : 0) * kRW + lane];
-    const float2 up0 = (wave > 0) ? up_lds : zero2;
+    const float2 up0 = sw[0];
 #pragma unroll
     for (int i = 0; i < P; ++i) {
       const int j = jb + i;
@@ -384,9 +400,8 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
 // HIST: also store r after every fused iteration (the adjoint's recomputation);
 // st_out then receives q only: the last r of the history is its r plane.
 template <int KIND, int CONSTR, bool MASK, int NW, int P, bool HIST = false>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void fgp_col_kernel(FgpPlainArgs P_) {
-  __shared__ float2 sBot[NW * kRW];
-  __shared__ float2 sTop[NW * kRW];
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NW, P)))) void fgp_col_kernel(FgpPlainArgs P_) {
+  __shared__ float2 sRows[2 * (NW + 1) * kRW];
   __shared__ float sBeta[kMaxFuse];
   if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = P_.beta[threadIdx.x];
   __syncthreads();
@@ -432,9 +447,9 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) vo
   const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (NW * P - 2 * H) - H;
   const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
   if (interior)
-    fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, HIST>(J, H, sBeta, sBot, sTop);
+    fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, HIST>(J, H, sBeta, sRows);
   else
-    fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, HIST>(J, H, sBeta, sBot, sTop);
+    fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, HIST>(J, H, sBeta, sRows);
 }
 
 // ---------------------------------------------------------------------------
@@ -474,8 +489,7 @@ __device__ void flow_fail_tile(float2* x, float4* st, int m, int n, int tx, int 
 template <int KIND, int CONSTR, bool MASK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void fgp_flow_kernel(FgpFlowArgs A) {
   constexpr int NW = 8, P = 8;
-  __shared__ float2 sBot[NW * kRW];
-  __shared__ float2 sTop[NW * kRW];
+  __shared__ float2 sRows[2 * (NW + 1) * kRW];
   __shared__ float sBeta[kMaxFuse];
   __shared__ int sTicket;
   __shared__ int sErr;
@@ -557,9 +571,9 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void f
     const int c0 = tx * (kRW - 2 * H) - H, r0 = ty * (NW * P - 2 * H) - H;
     const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
     if (interior)
-      fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, false, true>(J, H, sBeta, sBot, sTop);
+      fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, false, true>(J, H, sBeta, sRows);
     else
-      fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, false, true>(J, H, sBeta, sBot, sTop);
+      fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, false, true>(J, H, sBeta, sRows);
     __builtin_amdgcn_s_waitcnt(0);  // this wave's state stores are complete (device-coherent)
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_store(done_img + t, st + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -574,8 +588,7 @@ constexpr int kSingleNW = 16, kSingleP = 4;
 
 template <int KIND, int CONSTR, bool MASK>
 __global__ __launch_bounds__(kSingleNW * 64) void fgp_single_kernel(FgpSingleArgs A) {
-  __shared__ float2 sBot[kSingleNW * kRW];
-  __shared__ float2 sTop[kSingleNW * kRW];
+  __shared__ float2 sRows[2 * (kSingleNW + 1) * kRW];
   __shared__ float sBeta[kFlowMaxIters];
   for (int i = threadIdx.x; i < A.T; i += blockDim.x) sBeta[i] = A.beta[i];
   __syncthreads();
@@ -597,7 +610,7 @@ __global__ __launch_bounds__(kSingleNW * 64) void fgp_single_kernel(FgpSingleArg
   J.T = A.T;
   J.r_hist = nullptr;
   J.hist_stride = 0;
-  fgp_tile_col<KIND, CONSTR, MASK, kSingleNW, kSingleP, true>(J, 0, sBeta, sBot, sTop);
+  fgp_tile_col<KIND, CONSTR, MASK, kSingleNW, kSingleP, true>(J, 0, sBeta, sRows);
 }
 
 // ---------------------------------------------------------------------------
@@ -640,63 +653,59 @@ __global__ __launch_bounds__(kThreads) void fgp_plain_kernel(FgpPlainArgs P) {
 // ragged batch. The tile list of the step holds, per image still running, the
 // tiles laid out for that image's own halo (T_i + 1 when its last iteration
 // falls in this step, else T_i), so each image is computed exactly as a plain
-// call would. Each XCD owns one contiguous slice of the tile list and its
-// workgroups stride through it; the plan launches one workgroup per tile (a
-// persistent grid with static striding measured 15-20 % slower than letting
-// the hardware dispatcher balance), so the loop normally runs once.
+// call would. Each XCD owns one contiguous slice of the tile list; the grid has
+// at least one workgroup per entry (a persistent grid with static striding
+// measured 15-20 % slower than letting the hardware dispatcher balance) and a
+// workgroup runs one tile: a loop over tiles kept enough alive across the switch
+// to spill 71 registers of the 16 x 4 tile.
 // ---------------------------------------------------------------------------
 template <int CONSTR, int NW, int P>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(4))) void fgp_batched_kernel(FgpBatchedArgs A) {
-  __shared__ float2 sBot[NW * kRW];
-  __shared__ float2 sTop[NW * kRW];
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NW, P)))) void fgp_batched_kernel(FgpBatchedArgs A) {
+  __shared__ float2 sRows[2 * (NW + 1) * kRW];
   __shared__ float sBeta[kMaxFuse];
   if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = (threadIdx.x < A.T) ? A.beta_table[A.k0 + 1 + threadIdx.x] : 0.0f;
   __syncthreads();
   constexpr int kXcd = 8;
-  const int G = gridDim.x;
   const int xcd = blockIdx.x % kXcd, bi = blockIdx.x / kXcd;
-  const int gx = G / kXcd + (xcd < G % kXcd ? 1 : 0);
-  const int nrun = A.live ? A.live_count[0] : A.ntiles;
-  const int lo = (int)((long long)nrun * xcd / kXcd);
-  const int hi = (int)((long long)nrun * (xcd + 1) / kXcd);
-  for (int t = lo + bi; t < hi; t += gx) {
-    const BatchTile bt = A.tiles[A.live ? A.live[t] : t];
-    const BatchImage D = A.images[bt.image];
-    const int Ti = min(A.T, D.iters - A.k0);
-    const bool last = (A.k0 + Ti == D.iters);
-    const int H = max(1, Ti + (last ? 1 : 0));
-    TileJob J;
-    J.b = reinterpret_cast<const float2*>(A.b) + D.offset;
-    J.mask = (D.support_offset >= 0 && A.support) ? A.support + D.support_offset : nullptr;
-    J.st_in = (A.k0 == 0) ? nullptr : reinterpret_cast<const float4*>(A.st_in) + 2 * D.offset;
-    J.st_out = last ? nullptr : reinterpret_cast<float4*>(A.st_out) + 2 * D.offset;
-    J.x = last ? reinterpret_cast<float2*>(A.x) + D.offset : nullptr;
-    J.m = D.m;
-    J.n = D.n;
-    J.tx = bt.tx;
-    J.ty = bt.ty;
-    J.lam = D.lam;
-    J.c = D.c;
-    J.R = D.R;
-    J.T = Ti;
-    J.r_hist = nullptr;
-    J.hist_stride = 0;
-    const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (NW * P - 2 * H) - H;
-    const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
-    const int sel = (D.kind * 2 + (J.mask ? 1 : 0)) * 2 + (interior ? 0 : 1);
-    switch (sel) {
-#define CTV_B(KI, MK, BO, S)                                                             \
-  case S:                                                                                \
-    fgp_tile_col<KI, CONSTR, MK, NW, P, BO>(J, H, sBeta, sBot, sTop);                    \
+  const int nrun = A.live ? A.live_count[0] : A.ntiles;  // <= gridDim.x
+  const int each = nrun / kXcd, rem = nrun % kXcd;
+  if (bi >= each + (xcd < rem ? 1 : 0)) return;
+  const int t = xcd * each + min(xcd, rem) + bi;
+  const BatchTile bt = A.tiles[A.live ? A.live[t] : t];
+  const BatchImage D = A.images[bt.image];
+  const int Ti = min(A.T, D.iters - A.k0);
+  const bool last = (A.k0 + Ti == D.iters);
+  const int H = max(1, Ti + (last ? 1 : 0));
+  TileJob J;
+  J.b = reinterpret_cast<const float2*>(A.b) + D.offset;
+  J.mask = (D.support_offset >= 0 && A.support) ? A.support + D.support_offset : nullptr;
+  J.st_in = (A.k0 == 0) ? nullptr : reinterpret_cast<const float4*>(A.st_in) + 2 * D.offset;
+  J.st_out = last ? nullptr : reinterpret_cast<float4*>(A.st_out) + 2 * D.offset;
+  J.x = last ? reinterpret_cast<float2*>(A.x) + D.offset : nullptr;
+  J.m = D.m;
+  J.n = D.n;
+  J.tx = bt.tx;
+  J.ty = bt.ty;
+  J.lam = D.lam;
+  J.c = D.c;
+  J.R = D.R;
+  J.T = Ti;
+  J.r_hist = nullptr;
+  J.hist_stride = 0;
+  const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (NW * P - 2 * H) - H;
+  const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
+  const int sel = (D.kind * 2 + (J.mask ? 1 : 0)) * 2 + (interior ? 0 : 1);
+  switch (sel) {
+#define CTV_B(KI, MK, BO, S)                                     \
+  case S:                                                        \
+    fgp_tile_col<KI, CONSTR, MK, NW, P, BO>(J, H, sBeta, sRows); \
     break;
-      CTV_B(K1I, false, false, 0) CTV_B(K1I, false, true, 1) CTV_B(K1I, true, false, 2) CTV_B(K1I, true, true, 3)
-      CTV_B(K1A, false, false, 4) CTV_B(K1A, false, true, 5) CTV_B(K1A, true, false, 6) CTV_B(K1A, true, true, 7)
-      CTV_B(K2I, false, false, 8) CTV_B(K2I, false, true, 9) CTV_B(K2I, true, false, 10) CTV_B(K2I, true, true, 11)
-      CTV_B(K2A, false, false, 12) CTV_B(K2A, false, true, 13) CTV_B(K2A, true, false, 14)
-      default: fgp_tile_col<K2A, CONSTR, true, NW, P, true>(J, H, sBeta, sBot, sTop); break;
+    CTV_B(K1I, false, false, 0) CTV_B(K1I, false, true, 1) CTV_B(K1I, true, false, 2) CTV_B(K1I, true, true, 3)
+    CTV_B(K1A, false, false, 4) CTV_B(K1A, false, true, 5) CTV_B(K1A, true, false, 6) CTV_B(K1A, true, true, 7)
+    CTV_B(K2I, false, false, 8) CTV_B(K2I, false, true, 9) CTV_B(K2I, true, false, 10) CTV_B(K2I, true, true, 11)
+    CTV_B(K2A, false, false, 12) CTV_B(K2A, false, true, 13) CTV_B(K2A, true, false, 14)
+    default: fgp_tile_col<K2A, CONSTR, true, NW, P, true>(J, H, sBeta, sRows); break;
 #undef CTV_B
-    }
-    __syncthreads();  // the next tile reuses the LDS rows
   }
 }
 
