@@ -219,6 +219,11 @@ ctv_status ctv_batched_plan_create(const ctv_image_desc* descs, int32_t count, c
         fgp_batched_kernel_ptr(common->constraint, tuned.shape)) {
       clamp_fuse(&tuned, tp.iters);
       tl = tuned;
+    } else {
+      const long long o = 64 - 2 * std::max(1, tl.T);
+      long long tiles = 0;
+      for (const BatchImage& d : imgs) tiles += ((d.n + o - 1) / o) * ((d.m + o - 1) / o);
+      if (region_as_16x4(tiles)) tl.shape.waves = 16, tl.shape.rows_per_thread = 4;
     }
   }
   ctv_batched_plan* p = new ctv_batched_plan();

@@ -108,16 +108,33 @@ void clamp_fuse(Tiling* t, int iters) {
   t->T = std::max(t->T, 1);
 }
 
+// The automatic 64 x 64 region runs as 16 waves x 4 rows where it has more tiles
+// than CUs: two workgroups share a CU at 8 waves per SIMD, where the 8 x 8 form
+// has 4. Measured 8 x 8 -> 16 x 4, T = 8: 700^2 .. 8192^2, all kinds, -3 .. -8 %,
+// plans of 4 x 2048^2 2543 -> 2402 us, 64 images of 128 .. 1024 a side 3202 -> 3110.
+// With one tile per CU the two are within 4 % (small_tiling's costs). Without a
+// device (nothing can be launched) the plain default is reported.
+bool region_as_16x4(long long tiles) {
+  if (tiles <= 256) return false;
+  int devices = 0;
+  if (hipGetDeviceCount(&devices) != hipSuccess) {
+    (void)hipGetLastError();
+    return false;
+  }
+  return devices > 0;
+}
+
 // Tile shape and fusion depth for a run of `iters` iterations where one or two
 // tiles per CU cover the problem. A launch's time is then not bandwidth but the latency of
 // one tile, fixed + step T for T iterations (microseconds, fitted to launches of
 // T = 4 .. 14 on MI355X, within 6 %): smaller tiles start sooner and have fewer
 // rows to iterate, deeper fusion saves launches, and a larger halo is free as long
-// as the tiles do not outnumber the CUs. The 12 x 4 and 8 x 4 tiles are also
-// considered with two tiles per CU (both resident). These compete against the
-// default (8 x 8, T = 8) with the tiles it has. Measured, default ->
-// this choice, per iteration: 128^2 1.99 -> 1.09 us, 512^2 2.03 -> 1.51,
-// 12 x 150 x 203 1.98 -> 1.71, 700^2 2.23 -> 1.99, 850^2 3.13 -> 2.57. With more
+// as the tiles do not outnumber the CUs. The tiles of 4 rows a wave are also
+// considered with two per CU (both resident). These compete against the default
+// (T = 8: 8 x 8, or region_as_16x4 above one tile per CU) with the tiles it has.
+// Measured, 8 x 8 with T = 8 -> this choice, per iteration: 128^2 1.99 -> 1.09 us,
+// 512^2 2.02 -> 1.53, 12 x 150 x 203 2.03 -> 1.68, 700^2 2.23 -> 1.97, 850^2
+// 3.13 -> 2.61, 960^2 3.20 -> 2.80. With more
 // tiles per CU the shapes differ by less than the model's error (1000 x 1501 chosen
 // by it: 293 -> 326 us), so the line is drawn there.
 static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
@@ -126,9 +143,11 @@ static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
     double fixed, step;
   };
   static const Cost costs[] = {{8, 8, 1, 6.5, 1.20}, {12, 4, 1, 5.5, 0.92},  {8, 4, 1, 4.7, 0.81},
-                               {16, 4, 1, 7.2, 1.05}, {12, 4, 2, 12.4, 1.03}, {8, 4, 2, 6.5, 1.10}};
+                               {16, 4, 1, 7.2, 1.05}, {12, 4, 2, 12.4, 1.03}, {8, 4, 2, 6.5, 1.10},
+                               {16, 4, 2, 8.7, 1.93}};
   constexpr int kCus = 256, kMaxT = 14;
   const int images = std::min(batch, kPlainChunk);
+  const double px = (double)m * n * images;
   auto per_cu = [&](const Cost& c, int T) {
     const long long ow = 64 - 2 * T, oh = c.waves * c.rows - 2 * T;
     return (((n + ow - 1) / ow) * ((m + oh - 1) / oh) * images + kCus - 1) / kCus;
@@ -137,13 +156,17 @@ static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
   const long long k = iters > 0 ? per_cu(costs[0], std::min(8, iters)) : 0;
   if (k < 1 || k > 3) return;
   const int Td = (iters + launches(8) - 1) / launches(8);
-  double best = launches(8) * (3.5 + 3.0 * k + Td * (0.35 + 0.85 * k));
+  double best = launches(8) * (3.5 + 3.0 * k + Td * (0.35 + 0.85 * k)) * (k > 1 ? 0.95 : 1.0);
   // an image inside one 8 x 8 tile: the single-tile kernel's one launch
   if (m <= 64 && n <= 64) best = (iters + kFlowMaxIters - 1) / kFlowMaxIters * 5.0 + 1.18 * iters;
   for (const Cost& c : costs)
     for (int T = 1; T <= std::min({kMaxT, iters, c.waves * c.rows / 2 - 2}); ++T) {
       if ((iters + launches(T) - 1) / launches(T) != T || per_cu(c, T) > c.per_cu) continue;
-      const double us = launches(T) * (c.fixed + c.step * T);
+      // two 16 x 4 tiles a CU: below 8 iterations a launch is the memory's 21-23 us
+      if (c.rows * c.waves == 64 && c.per_cu == 2 && T < 8) continue;
+      // one tile a CU: the state leaves the L2s above about 360 k pixels
+      const double mem = c.per_cu == 1 ? std::max(0.0, px - 360e3) * 9e-6 : 0.0;
+      const double us = launches(T) * (c.fixed + mem + c.step * T);
       if (us < best) {
         best = us;
         out->shape.waves = c.waves;
@@ -168,10 +191,16 @@ ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* o
       return fail(CTV_ERR_INVALID_ARG, "unsupported tile shape");
   } else if (use_tuned && p->fuse == 0) {
     Tiling tuned;
-    if (tuned_lookup(plain_tune_key(p, batch, m, n), &tuned) && valid_tile_shape(tuned.shape))
+    if (tuned_lookup(plain_tune_key(p, batch, m, n), &tuned) && valid_tile_shape(tuned.shape)) {
       t = tuned;
-    else
-      small_tiling(m, n, batch, run > 0 ? std::min(run, p->iters) : p->iters, &t);
+    } else {
+      const int iters = run > 0 ? std::min(run, p->iters) : p->iters;
+      small_tiling(m, n, batch, iters, &t);
+      const long long o = 64 - 2 * std::max(1, std::min(8, iters));
+      if (t.shape.waves == 8 && t.shape.rows_per_thread == 8 &&
+          region_as_16x4(((n + o - 1) / o) * ((m + o - 1) / o) * std::min(batch, kPlainChunk)))
+        t.shape.waves = 16, t.shape.rows_per_thread = 4;
+    }
   }
   if (p->fuse > 0) t.T = p->fuse;
   clamp_fuse(&t, p->iters);

@@ -1,6 +1,6 @@
 """The automatic tile shape and fusion depth of small problems (one or two tiles per
 CU): host-side, every choice is a supported shape whose tiles fit the 256 CUs once
-(12 x 4 and 8 x 4: twice), or the default; on the GPU, an automatic call equals the 8 x 8 tile with 8
+(tiles of 4 rows a wave: twice), or the default depth and region; on the GPU, an automatic call equals the 8 x 8 tile with 8
 fused iterations bit for bit at the sizes where the choice changes."""
 import numpy as np
 import pytest
@@ -26,8 +26,9 @@ def test_choice_fits_the_cus_or_is_the_default(batch):
         for K in (1, 2, 7, 20, 100):
             T, rows, w, rp = ctv.tiling(0, K, m, n, batch=batch, detail=True)
             assert (w, rp) in SHAPES and rows == w * rp and 1 <= T <= K and T < rows // 2 - 1
-            if (w, rp, T) != (8, 8, min(8, K)):
-                assert tiles(m, n, batch, T, rows) <= (512 if (w, rp) in ((12, 4), (8, 4)) else 256), (m, n, K)
+            if (w * rp, T) != (64, min(8, K)):
+                two = rp == 4 and (w < 16 or T >= 8)
+                assert tiles(m, n, batch, T, rows) <= (512 if two else 256), (m, n, K)
             seen.add((w, rp))
     assert len(seen) > 1
 
