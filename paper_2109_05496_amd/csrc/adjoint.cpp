@@ -115,6 +115,8 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
   tp.iters = c;
   st = choose_tiling(&tp, m, n, batch, &tl);
   if (st) return st;
+  tl.shape.waves = 16;  // the form of the 64 x 64 region that stores the history
+  tl.shape.rows_per_thread = 4;
   std::vector<float> beta;
   momentum_table(p->method, K + 1, beta);
   const int halo = adj_halo(c);

@@ -238,8 +238,8 @@ ctv_status fgp_launch(const ctv_params* p, const Tiling& tl, int cb, int m, int 
                       const uint8_t* support, const float* lam, const std::vector<float>& beta, int k, int Tl,
                       const float* src, float* dst, float* x, hipStream_t s, float* r_hist,
                       long long r_hist_stride, const int* live) {
-  if (r_hist && (tl.shape.waves != 8 || tl.shape.rows_per_thread != 8))
-    return fail(CTV_ERR_INVALID_ARG, "r history needs the 8 x 8 column tile");
+  if (r_hist && (tl.shape.waves != 16 || tl.shape.rows_per_thread != 4))
+    return fail(CTV_ERR_INVALID_ARG, "r history needs the 16 x 4 column tile");
   FgpPlainArgs a;
   std::memset(&a, 0, sizeof(a));
   a.b = b;

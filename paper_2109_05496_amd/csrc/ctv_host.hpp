@@ -51,7 +51,7 @@ size_t denoise_ws_bytes(int batch, int m, int n);
 // One launch of the plain fused kernel: iterations k+1 .. k+Tl on a chunk of
 // cb <= 32 images (per-image lambdas lam[0..cb)), from state src (nullptr =
 // cold start) into dst (nullptr = not stored); x != nullptr adds Eq. (18).
-// r_hist != nullptr (8 x 8 column tile only) also stores r after each fused
+// r_hist != nullptr (16 x 4 column tile only) also stores r after each fused
 // iteration i into plane 1 of the state at r_hist + i * r_hist_stride floats.
 // live (column tiles only): the live-tile list of this tiling; the other tiles
 // are not run, so src and dst must already hold their (zero) values.
