@@ -76,7 +76,7 @@ typedef int32_t ctv_status;
  * CTV_S_FLOW needs ckpt_every = 0, iters > 0 and the default 8 x 8 column tile;
  * its tiles pass the dual state through device-coherent accesses and wait (a
  * bounded wait) for their neighbours. CTV_S_AUTO uses CTV_S_STEPS, which is
- * faster on MI355X, except that an image of at most 64 x 64 pixels (default
+ * faster on MI355X, except that an image of at most 64 x 64 pixels (8 x 8
  * tile, no checkpoints) runs up to 480 iterations per launch in one tile with
  * no halo. */
 #define CTV_S_AUTO 0
@@ -93,8 +93,10 @@ typedef struct {
   int32_t iters;        /* K >= 0, FGP iterations (Algorithm 2) */
   int32_t fuse;         /* at most this many iterations fused per kernel launch, 1..16 (a run is
                            split into the fewest launches, iterations spread evenly); 0 = automatic */
-  int32_t tile_waves;   /* tile shape (tuning): 0 = automatic; 4, 8 or 16 wave64s per workgroup in
-                           the column-register tile; -1 = the LDS-staged tile (4 waves); -2 = the
+  int32_t tile_waves;   /* tile shape (tuning): 0 = automatic (by the problem's size: smaller tiles
+                           and other depths where the default region's tiles leave CUs idle, 16 x 4
+                           waves x rows for the 64 x 64 region elsewhere); 4, 8, 12 or 16 wave64s per
+                           workgroup in the column-register tile; -1 = the LDS-staged tile (4 waves); -2 = the
                            row-sweep tile (8 waves sweeping down a 64-column strip one iteration
                            behind each other, no vertical halo; at most 10 fused iterations) */
   int32_t tile_rows;    /* rows per thread: 0 = automatic; column tile 4 or 8 (with waves 4: 8 only);
@@ -252,7 +254,7 @@ ctv_status ctv_batched_plan_tiling(const ctv_batched_plan* plan, int32_t* fuse_o
  * batch, m, n, iters); the support mask is not part of the key. ctv_denoise,
  * ctv_tiling and pr_prox_grad (its inner prox) use a recorded entry whenever
  * params.fuse, tile_waves and tile_rows are all 0 (and schedule is not
- * CTV_S_FLOW); ctv_denoise_backward always uses the default.
+ * CTV_S_FLOW); ctv_denoise_backward always uses the 64 x 64 region.
  * ctv_batched_autotune does the same for a batched plan: it builds, runs and
  * destroys one plan per candidate and records the fastest under a key derived
  * from (constraint, method, and per image m, n, effective K, tv_kind, has
