@@ -39,6 +39,25 @@ def test_automatic_equals_8x8(batch, m, n, kind, masked):
     assert torch.equal(bits(z), bits(rz)) and torch.equal(bits(saved), bits(rsaved))
 
 
+@pytest.mark.parametrize("ckpt", [8, 9, 11, 12])
+def test_checkpoint_interval_in_one_launch_equals_8x8(ckpt):
+    import torch
+    import paper_2109_05496_amd as ctv
+    if not torch.cuda.is_available():
+        pytest.skip("needs a GPU")
+    ctv.tune_cache_clear()
+    g = torch.Generator(device="cuda").manual_seed(ckpt)
+    b = torch.view_as_complex(torch.randn(2, 601, 517, 2, device="cuda", generator=g)).contiguous()
+    support = (torch.rand(601, 517, device="cuda", generator=g) < 0.6).to(torch.uint8)
+    support[:100] = 0
+    for kind, mask, K in (("1i", None, 2 * ckpt), ("2a", support, 2 * ckpt + 3), ("1a", support, ckpt), ("2i", None, 7)):
+        kw = dict(kind=kind, alpha=0.3, support=mask, iters=K, ckpt_every=ckpt, gap=True)
+        x, gap, saved = ctv.denoise(b, 0.06, **kw)
+        rx, rgap, rsaved = ctv.denoise(b, 0.06, fuse=8, tile=(8, 8), **kw)
+        assert torch.equal(bits(x), bits(rx)) and torch.equal(gap, rgap), (kind, K)
+        assert (saved is None and rsaved is None) or torch.equal(bits(saved), bits(rsaved)), (kind, K)
+
+
 @pytest.mark.parametrize("count,lo,hi", [(3, 500, 700), (60, 40, 200)])
 def test_ragged_plan_equals_8x8(count, lo, hi):
     import torch
