@@ -186,7 +186,7 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
         float* last = slot(k + Tl - 1 - ks);
         const bool q_read = k + Tl < kstop || sgi == nseg - 1;
         st = fgp_launch(p, tl, cb, m, n, a.b, support, lambda_host + c0, beta, k, Tl, prev, q_read ? last : nullptr,
-                        nullptr, s, slot(k - ks), (long long)(st_stride / 4));
+                        nullptr, s, slot(k - ks), (long long)(st_stride / 4), nullptr, k <= ks + 1);
         if (st) return st;
         prev = last;
         k += Tl;

@@ -244,7 +244,7 @@ size_t denoise_ws_bytes(int batch, int m, int n) {
 ctv_status fgp_launch(const ctv_params* p, const Tiling& tl, int cb, int m, int n, const float* b,
                       const uint8_t* support, const float* lam, const std::vector<float>& beta, int k, int Tl,
                       const float* src, float* dst, float* x, hipStream_t s, float* r_hist,
-                      long long r_hist_stride, const int* live) {
+                      long long r_hist_stride, const int* live, bool foreign) {
   if (r_hist && (tl.shape.waves != 16 || tl.shape.rows_per_thread != 4))
     return fail(CTV_ERR_INVALID_ARG, "r history needs the 16 x 4 column tile");
   FgpPlainArgs a;
@@ -259,6 +259,7 @@ ctv_status fgp_launch(const ctv_params* p, const Tiling& tl, int cb, int m, int 
     a.c[i] = step_of(lam[i]);
   }
   a.st_in = src;
+  a.foreign = src && foreign ? 1 : 0;
   a.st_out = dst;
   a.x = x;
   a.r_hist = r_hist;
@@ -516,7 +517,7 @@ ctv_status ctv_denoise(const ctv_params* p, int32_t batch, int32_t m, int32_t n,
           if (slot >= 0) live = live_mem + slot * slot_ints + live_cap(m, n);
         }
         st = fgp_launch(p, tl, cb, m, n, b + 2 * img_px, support, lambda_host + c0, beta, k, Tl, src, dst,
-                        last ? x + 2 * img_px : nullptr, s, nullptr, 0, live);
+                        last ? x + 2 * img_px : nullptr, s, nullptr, 0, live, state_in && k <= k0 + 1);
         if (st) return st;
         src = dst;
         k += Tl;

@@ -18,14 +18,33 @@ namespace ctv {
 
 // Hardware reciprocal square root (v_rsq_f32, ~1 ulp). Its arguments here are
 // sums of squares: a denormal argument is read as 0 and gives +inf, which the
-// callers' sat() maps to a unit scale - the right answer for a vector that
-// small.
+// callers' unit_scale() maps to a unit scale - the right answer for a vector
+// that small.
 __device__ __forceinline__ float rsq(float x) { return __builtin_amdgcn_rsqf(x); }
 
-// min(1, v) of a scale v >= 0 (or +inf; a NaN gives 0), written so that it
-// becomes the clamp modifier of the instruction that makes v: v_min_f32 issues
-// at half the rate of v_mul_f32 on gfx950, the modifier costs nothing.
-__device__ __forceinline__ float sat(float v) { return fminf(fmaxf(v, 0.0f), 1.0f); }
+// min(1, v) of a scale v >= 0 (or +inf). A NaN scale is 1, so that a NaN stays in
+// the entries that hold it and the others of its group keep their values. FIN:
+// the caller knows that v is no NaN, and the minimum becomes the clamp modifier of
+// the instruction that makes v (a NaN would give 0): v_min_f32 issues at half the
+// rate of v_mul_f32 on gfx950, the modifier costs nothing.
+template <bool FIN>
+__device__ __forceinline__ float unit_scale(float v) {
+  return FIN ? fminf(fmaxf(v, 0.0f), 1.0f) : fminf(1.0f, v);
+}
+
+// The scale of a ball of radius rho >= 0 for a vector of squared norm n2. rho = 0
+// gives 0 * inf = NaN at n2 = 0; the scale is 0 there as for every other n2.
+template <bool FIN>
+__device__ __forceinline__ float ball_scale(float rho, float n2) {
+  const float s = unit_scale<true>(rho * rsq(n2));
+  return FIN || n2 == n2 ? s : 1.0f;
+}
+
+// Inputs below this magnitude keep every value of the iteration finite: with
+// |b|, |q|, |r| and lambda below 1e18 the gradient step is at most 1e37 and the
+// duals leave it inside the unit ball (a squared norm that overflows gives the
+// scale 0).
+constexpr float kFiniteRange = 1e18f;
 
 // A value that is the same in every lane, held in a vector register: on gfx950
 // v_fma_f32, v_mul_f32 and v_add_f32 with a scalar-register operand issue at
@@ -40,12 +59,12 @@ __device__ __forceinline__ float in_vgpr(float v) {
 // on, then forced to 0 outside the support (a zero scale; adding +0 to the
 // product turns -0 into +0, so masked pixels hold exactly +0 whatever the sign
 // of w, and a tile that is never computed matches one that is).
-template <int CONSTR>
+template <int CONSTR, bool FIN = false>
 __device__ __forceinline__ float2 proj_c(float2 w, bool inside) {
   float2 y = w;
   if (CONSTR == C_MOD) {
     const float n2 = fmaf(w.x, w.x, w.y * w.y);
-    float s = sat(rsq(n2));  // 1/max{1,|w|}; rsqrt(0) = inf gives 1
+    float s = unit_scale<FIN>(rsq(n2));  // 1/max{1,|w|}; rsqrt(0) = inf gives 1
     s = inside ? s : 0.0f;
     y.x = fmaf(w.x, s, 0.0f);  // the product, with +0 in place of -0
     y.y = fmaf(w.y, s, 0.0f);
@@ -63,25 +82,24 @@ __device__ __forceinline__ float2 proj_c(float2 w, bool inside) {
 // Each scale is min(1, radius / norm), i.e. the paper's radius / max{radius, norm}.
 // Type 2a (Eq. 37) clips each real entry to [-alpha, alpha] or
 // [-(1-alpha), 1-alpha] instead and has no scale form.
-template <int KIND>
+template <int KIND, bool FIN = false>
 __device__ __forceinline__ float4 ps_scale(float4 g, const Radii& R) {
   if (KIND == K1I) {
     const float n2 = fmaf(g.x, g.x, fmaf(g.y, g.y, fmaf(g.z, g.z, g.w * g.w)));
-    const float s = sat(rsq(n2));
+    const float s = unit_scale<FIN>(rsq(n2));
     return make_float4(s, s, s, s);
   } else if (KIND == K1A) {
     const float n1 = fmaf(g.x, g.x, g.y * g.y);
     const float n2 = fmaf(g.z, g.z, g.w * g.w);
-    const float s1 = sat(rsq(n1));
-    const float s2 = sat(rsq(n2));
+    const float s1 = unit_scale<FIN>(rsq(n1));
+    const float s2 = unit_scale<FIN>(rsq(n2));
     return make_float4(s1, s1, s2, s2);
   } else {
-    // rho / max{rho, ||v||} = min(1, rho / ||v||); a zero radius gives 0 * inf = NaN
-    // at v = 0, which sat turns into 0, and 0 * v = 0 either way.
+    // rho / max{rho, ||v||} = min(1, rho / ||v||)
     const float nr = fmaf(g.x, g.x, g.z * g.z);
     const float ns = fmaf(g.y, g.y, g.w * g.w);
-    const float fr = sat(R.ra * rsq(nr));
-    const float fs = sat(R.sa * rsq(ns));
+    const float fr = ball_scale<FIN>(R.ra, nr);
+    const float fs = ball_scale<FIN>(R.sa, ns);
     return make_float4(fr, fs, fr, fs);
   }
 }
@@ -92,7 +110,7 @@ __device__ __forceinline__ float4 ps_scale(float4 g, const Radii& R) {
 // per entry for the scaled kinds) and q_k = q_{k-1} + d, so the update writes
 // q's registers in place: three operations per entry, and q_k within a
 // rounding of P_S(g).
-template <int KIND>
+template <int KIND, bool FIN = false>
 __device__ __forceinline__ void dual_update(float4 g, const Radii& R, float beta, float4& q, float4& r) {
   float dx, dy, dz, dw;
   if (KIND == K2A) {
@@ -103,7 +121,7 @@ __device__ __forceinline__ void dual_update(float4 g, const Radii& R, float beta
     dz = __builtin_amdgcn_fmed3f(g.z, -R.ra, R.ra) - q.z;
     dw = __builtin_amdgcn_fmed3f(g.w, -R.sa, R.sa) - q.w;
   } else {
-    const float4 s = ps_scale<KIND>(g, R);
+    const float4 s = ps_scale<KIND, FIN>(g, R);
     dx = fmaf(g.x, s.x, -q.x);
     dy = fmaf(g.y, s.y, -q.y);
     dz = fmaf(g.z, s.z, -q.z);
@@ -139,8 +157,8 @@ __device__ __forceinline__ float4 dual_step(float4 r, float2 y, float2 down, flo
   return g;
 }
 
-// The same with the step of each direction given (0 where that difference does
-// not exist; the caller's r is 0 there, so g is too).
+// The same with the step of each direction given: 0 where that difference does
+// not exist. The caller's r is 0 there, so g is too as long as y is finite.
 __device__ __forceinline__ float4 dual_step(float4 r, float2 y, float2 down, float2 right, float cv, float ch) {
   return make_float4(fmaf(cv, y.x - down.x, r.x), fmaf(cv, y.y - down.y, r.y), fmaf(ch, y.x - right.x, r.z),
                      fmaf(ch, y.y - right.y, r.w));

@@ -13,6 +13,7 @@ struct FgpPlainArgs {
   const float* b;        // chunk base, [chunk][m][n] complex64
   const uint8_t* mask;   // [m][n] or nullptr
   const float* st_in;    // [chunk][2][m][n][4] or nullptr (cold start)
+  int foreign;           // st_in is a caller's state, or one iteration from it (r still holds the caller's q)
   float* st_out;         // same layout or nullptr
   float* x;              // [chunk][m][n] complex64 or nullptr
   int m, n;

@@ -14,10 +14,12 @@ struct TileJob {
   const float2* b;       // image (m x n)
   const uint8_t* mask;   // image support or nullptr
   const float4* st_in;   // [2][m][n] (q plane, r plane) or nullptr = cold start
+  bool foreign;          // st_in is a caller's state, or one iteration from it (column tiles)
   float4* st_out;        // [2][m][n] or nullptr
   float2* x;             // Eq. (18) output or nullptr
   int m, n;
   int tx, ty;
+  int kind;              // read by the kernel that runs all kinds in one body only
   float lam, c;
   Radii R;
   int T;

@@ -38,7 +38,7 @@ template <int CONSTR>
 __device__ __forceinline__ float2 proj_c_s(float2 w, bool inside, float& s) {
   if (CONSTR == C_MOD) {
     const float n2 = fmaf(w.x, w.x, w.y * w.y);
-    s = sat(rsq(n2));
+    s = unit_scale<true>(rsq(n2));
     const float sm = inside ? s : 0.0f;
     return make_float2(fmaf(w.x, sm, 0.0f), fmaf(w.y, sm, 0.0f));
   }
@@ -83,18 +83,18 @@ __device__ __forceinline__ float4 proj_s_vjp(float4 g, float4 a, const Radii& R)
   float4 o;
   if (KIND == K1I) {
     const float n2 = fmaf(g.x, g.x, fmaf(g.y, g.y, fmaf(g.z, g.z, g.w * g.w)));
-    const float s = sat(rsq(n2));
+    const float s = unit_scale<true>(rsq(n2));
     const float t = fmaf(g.x, a.x, fmaf(g.y, a.y, fmaf(g.z, a.z, g.w * a.w))) * (s * s);
     const float d = s < 1.0f ? t : 0.0f;  // inactive: o = a
     o = make_float4(s * fmaf(-g.x, d, a.x), s * fmaf(-g.y, d, a.y), s * fmaf(-g.z, d, a.z), s * fmaf(-g.w, d, a.w));
   } else if (KIND == K1A) {
-    const float s1 = sat(rsq(fmaf(g.x, g.x, g.y * g.y)));
-    const float s2 = sat(rsq(fmaf(g.z, g.z, g.w * g.w)));
+    const float s1 = unit_scale<true>(rsq(fmaf(g.x, g.x, g.y * g.y)));
+    const float s2 = unit_scale<true>(rsq(fmaf(g.z, g.z, g.w * g.w)));
     ball_vjp2(g.x, g.y, a.x, a.y, s1, 1.0f, o.x, o.y);
     ball_vjp2(g.z, g.w, a.z, a.w, s2, 1.0f, o.z, o.w);
   } else if (KIND == K2I) {
-    const float fr = sat(R.ra * rsq(fmaf(g.x, g.x, g.z * g.z)));
-    const float fs = sat(R.sa * rsq(fmaf(g.y, g.y, g.w * g.w)));
+    const float fr = ball_scale<true>(R.ra, fmaf(g.x, g.x, g.z * g.z));
+    const float fs = ball_scale<true>(R.sa, fmaf(g.y, g.y, g.w * g.w));
     ball_vjp2(g.x, g.z, a.x, a.z, fr, R.ra, o.x, o.z);
     ball_vjp2(g.y, g.w, a.y, a.w, fs, R.sa, o.y, o.w);
   } else {

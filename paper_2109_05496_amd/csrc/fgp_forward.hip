@@ -30,9 +30,9 @@ constexpr int kWaves = kThreads / 64;
 
 
 template <int KIND, int CONSTR, bool MASK, int RH>
-__device__ __forceinline__ void fgp_tile(const TileJob& J, const int H, const float* sBeta,
-                                         float2* __restrict__ sA1, float2* __restrict__ sA2,
-                                         float2* __restrict__ sY) {
+__device__ __forceinline__ void fgp_tile_lds(const TileJob& J, const int H, const float* sBeta,
+                                             float2* __restrict__ sA1, float2* __restrict__ sA2,
+                                             float2* __restrict__ sY) {
   constexpr int PPT = RH / kWaves;
   const int lane = threadIdx.x & 63;
   const int wave = threadIdx.x >> 6;
@@ -189,9 +189,34 @@ constexpr int waves_per_simd(int NW, int P) { return NW == 16 && P == 4 ? 8 : 4;
 // 211 -> 185 us, 12 x 150 x 203 x 40 109 -> 95 us. Rows are skipped once they fall outside the
 // part of the region that can still reach the output (the shrinking trapezoid
 // of the fused iterations); one row more than the q rows needs y.
-template <int KIND, int CONSTR, bool MASK, int NW, int P, bool BORDER, bool HIST = false, bool COH = false>
-__device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, const float* sBeta,
-                                             float2* __restrict__ sRows) {
+//
+// FIN = true is the iteration for finite values: scales through the clamp modifier,
+// zero steps. It returns false, with nothing stored, where the region holds an input
+// that is not finite or too large to stay so (*sOdd, 0 on entry; 4 operations a pixel
+// and a barrier once a launch, 0.2 us of 4.3 to 12 of the 8 x 4 tile, about 2 % of a
+// masked 2048^2 call; q is finite where r is, unless the state is a caller's, which may
+// also hold a dual where none exists). FIN = false (with BORDER = true: it takes any
+// tile) selects what does not exist and keeps a NaN in the entries that hold it, as the
+// other tiles' kernels do: the same bits on finite values, and it never returns false.
+// One form for all inputs would cost a half-rate minimum per scale and two to four
+// masks a pixel in every iteration. KIND = kAnyKind (FIN = false only): the job's kind
+// and mask, as one body for all (the batched kernel would hold eight, and spill in its
+// other form).
+constexpr int kAnyKind = 4;
+__device__ __forceinline__ void dual_update_any(int kind, float4 g, const Radii& R, float beta, float4& q, float4& r) {
+  if (kind == K1I)
+    dual_update<K1I>(g, R, beta, q, r);
+  else if (kind == K1A)
+    dual_update<K1A>(g, R, beta, q, r);
+  else if (kind == K2I)
+    dual_update<K2I>(g, R, beta, q, r);
+  else
+    dual_update<K2A>(g, R, beta, q, r);
+}
+
+template <int KIND, int CONSTR, bool MASK, int NW, int P, bool BORDER, bool HIST, bool COH, bool FIN>
+__device__ __forceinline__ bool fgp_tile_col(const TileJob& J, const int H, const float* sBeta,
+                                             float2* __restrict__ sRows, int* sOdd) {
   constexpr int RH = NW * P;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -228,12 +253,13 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
     R.ra = in_vgpr(R.ra);
     R.sa = in_vgpr(R.sa);
   }
-  // Steps of the vertical and horizontal differences: 0 where the lower / right
-  // neighbour lies outside the image (and outside the image itself), which
-  // keeps the duals that do not exist at exactly 0 without a select, so a
+  // Which differences exist, and their steps: 0 where the lower / right neighbour
+  // lies outside the image (and outside the image itself), which keeps the duals
+  // that do not exist at exactly 0 without a select as long as y is finite, so a
   // neighbour outside the image always reads as 0 above and to the left.
-  const float ch = (!BORDER || (k >= 0 && k < J.n - 1)) ? c : 0.0f;
-  auto row_step = [&](int j) { return (j >= 0 && j < J.m - 1) ? J.c : 0.0f; };
+  auto has_down = [&](int j) { return !BORDER || (j >= 0 && j < J.m - 1); };
+  const bool has_right = !BORDER || (k >= 0 && k < J.n - 1);
+  const float ch = has_right ? c : 0.0f;
   float4 q[P], r[P];
   float2 b[P];
   bool inside[P];
@@ -264,7 +290,10 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
       const bool row_in = jb + i >= 0 && jb + i < J.m;
       const long long o = row_in ? (long long)(jb + i) * J.n + cl : 0;
       b[i] = buf_ld2(row_buf(J.b + o, row_in ? width * 8 : 0), off8);
-      inside[i] = MASK ? buf_ld_mask(row_buf(J.mask + o, row_in ? width : 0), off1) : true;
+      if (KIND == kAnyKind)
+        inside[i] = !J.mask || buf_ld_mask(row_buf(J.mask ? J.mask + o : nullptr, row_in && J.mask ? width : 0), off1);
+      else
+        inside[i] = MASK ? buf_ld_mask(row_buf(J.mask + o, row_in ? width : 0), off1) : true;
       if (!J.st_in) {
         q[i] = r[i] = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
       }
@@ -309,6 +338,32 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
   float2 y[P];
 #pragma unroll
   for (int i = 0; i < P; ++i) y[i] = zero2;
+  if (FIN) {
+    // r as products of pairs: one of these kernels' is at most 3 or not finite
+    float mag = J.lam;
+#pragma unroll
+    for (int i = 0; i < P; ++i) {
+      mag += fabsf(b[i].x) + fabsf(b[i].y);
+      mag = fmaf(r[i].z, r[i].w, fmaf(r[i].x, r[i].y, mag));
+    }
+    bool plain = fabsf(mag) < kFiniteRange;
+    if (J.foreign) {
+      unsigned extra = 0;
+#pragma unroll
+      for (int i = 0; i < P; ++i) {
+        mag += (fabsf(q[i].x) + fabsf(q[i].y)) + (fabsf(q[i].z) + fabsf(q[i].w));
+        mag += (fabsf(r[i].x) + fabsf(r[i].y)) + (fabsf(r[i].z) + fabsf(r[i].w));
+        if (BORDER && !has_down(jb + i))
+          extra |= __float_as_uint(q[i].x) | __float_as_uint(q[i].y) | __float_as_uint(r[i].x) | __float_as_uint(r[i].y);
+        if (BORDER && !has_right)
+          extra |= __float_as_uint(q[i].z) | __float_as_uint(q[i].w) | __float_as_uint(r[i].z) | __float_as_uint(r[i].w);
+      }
+      plain = plain && fabsf(mag) < kFiniteRange && extra == 0;
+    }
+    if (__builtin_amdgcn_ballot_w64(!plain)) *sOdd = 1;
+    __syncthreads();
+    if (__builtin_amdgcn_readfirstlane(*sOdd)) return false;
+  }
   for (int it = 0; it < J.T; ++it) {
     // Live rows of this wave as bit masks (uniform): y on [lo, hi], q on [lo, hi).
     const int lo = it + 1 + eu - wave * P, hi = RH - (it + 1) - ed - wave * P;
@@ -321,7 +376,7 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
       if (ym & (1u << i)) {
         const float lx = lane_from_left(r[i].z), ly = lane_from_left(r[i].w);
         const float2 up = (i > 0) ? make_float2(r[i - 1].x, r[i - 1].y) : up0;
-        y[i] = proj_c<CONSTR>(dual_to_primal(b[i], r[i], up, make_float2(lx, ly), lam), inside[i]);
+        y[i] = proj_c<CONSTR, FIN>(dual_to_primal(b[i], r[i], up, make_float2(lx, ly), lam), inside[i]);
       }
     }
     sw[kTop] = y[0];
@@ -334,8 +389,15 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
         const int j = jb + i;
         const float rx = lane_from_right(y[i].x), rv = lane_from_right(y[i].y);
         const float2 down = (i < P - 1) ? y[i + 1] : down_last;
-        const float4 g = dual_step(r[i], y[i], down, make_float2(rx, rv), BORDER ? row_step(j) : c, ch);
-        dual_update<KIND>(g, R, beta, q[i], r[i]);
+        float4 g;
+        if (BORDER && !FIN)
+          g = dual_step(r[i], y[i], down, make_float2(rx, rv), c, has_down(j), has_right);
+        else
+          g = dual_step(r[i], y[i], down, make_float2(rx, rv), BORDER ? (has_down(j) ? J.c : 0.0f) : c, ch);
+        if (KIND == kAnyKind)
+          dual_update_any(J.kind, g, R, beta, q[i], r[i]);
+        else
+          dual_update<KIND, FIN>(g, R, beta, q[i], r[i]);
       }
     }
     if (HIST) {
@@ -395,18 +457,44 @@ __device__ __forceinline__ void fgp_tile_col(const TileJob& J, const int H, cons
       }
     }
   }
+  return true;
 }
 
-// HIST: also store r after every fused iteration (the adjoint's recomputation);
-// st_out then receives q only: the last r of the history is its r plane.
-// 16 x 4 tile only, whose 8 waves per SIMD hide its stores better than 8 x 8 at 4:
-// backward pass of 16 x 512^2 2944 -> 2895 us, 256^2 276 -> 264.
-template <int KIND, int CONSTR, bool MASK, int NW, int P, bool HIST = false>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NW, P)))) void fgp_col_kernel(FgpPlainArgs P_) {
-  __shared__ float2 sRows[2 * (NW + 1) * kRW];
-  __shared__ float sBeta[kMaxFuse];
-  if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = P_.beta[threadIdx.x];
-  __syncthreads();
+// Whether the region of a tile lies at least one pixel inside the image on every side.
+template <int NW, int P>
+__device__ __forceinline__ bool interior_tile(const TileJob& J, int H) {
+  const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (NW * P - 2 * H) - H;
+  return c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
+}
+
+// One tile in the FIN = true form; returns whether that was done.
+template <int KIND, int CONSTR, bool MASK, int NW, int P, bool HIST = false, bool COH = false>
+__device__ __forceinline__ int finite_tile(const TileJob& J, const int H, const float* sBeta,
+                                           float2* __restrict__ sRows, int* sOdd) {
+  if (interior_tile<NW, P>(J, H)) return fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, HIST, COH, true>(J, H, sBeta, sRows, sOdd);
+  return fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, HIST, COH, true>(J, H, sBeta, sRows, sOdd);
+}
+
+// The FIN = false form follows in the same kernel, behind a value that the compiler
+// cannot look through and with the job read again from the kernel's arguments:
+// otherwise it places the second form before the loop of the first and keeps the
+// first's registers through it (63 -> 102 of the 8 x 4 tile), or keeps the job in
+// scalar registers that the first form spills (16 x 4: 2-3 % of a masked launch).
+__device__ __forceinline__ bool opaque(int done) {
+  done = __builtin_amdgcn_readfirstlane(done);
+  asm volatile("" : "+s"(done) : : "memory");
+  return __builtin_expect(done != 0, 1);
+}
+template <class A>
+__device__ __forceinline__ const A& args_again() {  // of a kernel whose only argument is an A
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const A*)p;
+}
+
+// The tile of this workgroup; false if it has none (live-tile list shorter than the grid).
+template <bool HIST>
+__device__ __forceinline__ bool plain_job(const FgpPlainArgs& P_, TileJob& J) {
   const int per_img = P_.tiles_x * P_.tiles_y;
   int img, t;
   if (P_.live) {
@@ -419,7 +507,7 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_p
     constexpr int kXcd = 8;
     const int x = blockIdx.x % kXcd, i = blockIdx.x / kXcd;
     const int q = total / kXcd, rem = total % kXcd;
-    if (i >= q + (x < rem ? 1 : 0)) return;
+    if (i >= q + (x < rem ? 1 : 0)) return false;
     const int e = x * q + (x < rem ? x : rem) + i;
     img = e / L;
     t = P_.live[1 + (e - img * L)];
@@ -429,10 +517,10 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_p
     t = tile - img * per_img;
   }
   const long long px = (long long)P_.m * P_.n;
-  TileJob J;
   J.b = reinterpret_cast<const float2*>(P_.b) + img * px;
   J.mask = P_.mask;
   J.st_in = P_.st_in ? reinterpret_cast<const float4*>(P_.st_in) + img * 2 * px : nullptr;
+  J.foreign = P_.foreign != 0;
   J.st_out = P_.st_out ? reinterpret_cast<float4*>(P_.st_out) + img * 2 * px : nullptr;
   J.x = P_.x ? reinterpret_cast<float2*>(P_.x) + img * px : nullptr;
   J.m = P_.m;
@@ -445,13 +533,27 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_p
   J.T = P_.T;
   J.r_hist = HIST ? reinterpret_cast<float4*>(P_.r_hist) + img * 2 * px + px : nullptr;
   J.hist_stride = P_.r_hist_stride / 4;
-  const int H = P_.halo;
-  const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (NW * P - 2 * H) - H;
-  const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
-  if (interior)
-    fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, HIST>(J, H, sBeta, sRows);
-  else
-    fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, HIST>(J, H, sBeta, sRows);
+  return true;
+}
+
+// HIST: also store r after every fused iteration (the adjoint's recomputation);
+// st_out then receives q only: the last r of the history is its r plane.
+// 16 x 4 tile only, whose 8 waves per SIMD hide its stores better than 8 x 8 at 4:
+// backward pass of 16 x 512^2 2944 -> 2895 us, 256^2 276 -> 264.
+template <int KIND, int CONSTR, bool MASK, int NW, int P, bool HIST = false>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NW, P)))) void fgp_col_kernel(FgpPlainArgs P_) {
+  __shared__ float2 sRows[2 * (NW + 1) * kRW];
+  __shared__ int sOdd;
+  __shared__ float sBeta[kMaxFuse];
+  if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = P_.beta[threadIdx.x];
+  if (threadIdx.x == 0) sOdd = 0;
+  __syncthreads();
+  TileJob J;
+  if (!plain_job<HIST>(P_, J)) return;
+  if (opaque(finite_tile<KIND, CONSTR, MASK, NW, P, HIST>(J, P_.halo, sBeta, sRows, &sOdd))) return;
+  const FgpPlainArgs& again = args_again<FgpPlainArgs>();
+  plain_job<HIST>(again, J);
+  fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, HIST, false, false>(J, again.halo, sBeta, sRows, &sOdd);
 }
 
 // ---------------------------------------------------------------------------
@@ -492,6 +594,7 @@ template <int KIND, int CONSTR, bool MASK>
 __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void fgp_flow_kernel(FgpFlowArgs A) {
   constexpr int NW = 8, P = 8;
   __shared__ float2 sRows[2 * (NW + 1) * kRW];
+  __shared__ int sOdd;
   __shared__ float sBeta[kMaxFuse];
   __shared__ int sTicket;
   __shared__ int sErr;
@@ -536,6 +639,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void f
     const bool epi = (st == A.steps);
     const int T = epi ? 0 : (st == A.steps - 1 ? A.T_last : A.T);
     if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = ((int)threadIdx.x < T) ? A.beta[st * A.T + threadIdx.x] : 0.0f;
+    if (threadIdx.x == 0) sOdd = 0;
     if (threadIdx.x == 0) sErr = epi ? __hip_atomic_load(A.err, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : 0;
     __syncthreads();
     float* in_buf = (st % 2 == 0) ? A.buf0 : A.buf1;
@@ -558,6 +662,7 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void f
     J.b = reinterpret_cast<const float2*>(A.b) + img * px;
     J.mask = A.mask;
     J.st_in = src ? reinterpret_cast<const float4*>(src) + img * 2 * px : nullptr;
+    J.foreign = A.st_in && st * A.T <= 1;
     J.st_out = dst ? reinterpret_cast<float4*>(dst) + img * 2 * px : nullptr;
     J.x = (epi && A.x) ? reinterpret_cast<float2*>(A.x) + img * px : nullptr;  // no x before the last chunk
     J.m = A.m;
@@ -570,12 +675,8 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void f
     J.T = T;
     J.r_hist = nullptr;
     J.hist_stride = 0;
-    const int c0 = tx * (kRW - 2 * H) - H, r0 = ty * (NW * P - 2 * H) - H;
-    const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
-    if (interior)
-      fgp_tile_col<KIND, CONSTR, MASK, NW, P, false, false, true>(J, H, sBeta, sRows);
-    else
-      fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, false, true>(J, H, sBeta, sRows);
+    if (!opaque(finite_tile<KIND, CONSTR, MASK, NW, P, false, true>(J, H, sBeta, sRows, &sOdd)))
+      fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, false, true, false>(J, H, sBeta, sRows, &sOdd);
     __builtin_amdgcn_s_waitcnt(0);  // this wave's state stores are complete (device-coherent)
     __syncthreads();
     if (threadIdx.x == 0) __hip_atomic_store(done_img + t, st + 1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
@@ -588,18 +689,13 @@ __global__ __launch_bounds__(512) __attribute__((amdgpu_waves_per_eu(4))) void f
 // rows per wave, i.e. shorter dependent chains for this latency-bound case.
 constexpr int kSingleNW = 16, kSingleP = 4;
 
-template <int KIND, int CONSTR, bool MASK>
-__global__ __launch_bounds__(kSingleNW * 64) void fgp_single_kernel(FgpSingleArgs A) {
-  __shared__ float2 sRows[2 * (kSingleNW + 1) * kRW];
-  __shared__ float sBeta[kFlowMaxIters];
-  for (int i = threadIdx.x; i < A.T; i += blockDim.x) sBeta[i] = A.beta[i];
-  __syncthreads();
+__device__ __forceinline__ void single_job(const FgpSingleArgs& A, TileJob& J) {
   const int img = blockIdx.x;
   const long long px = (long long)A.m * A.n;
-  TileJob J;
   J.b = reinterpret_cast<const float2*>(A.b) + img * px;
   J.mask = A.mask;
   J.st_in = A.st_in ? reinterpret_cast<const float4*>(A.st_in) + img * 2 * px : nullptr;
+  J.foreign = A.st_in != nullptr;
   J.st_out = A.st_out ? reinterpret_cast<float4*>(A.st_out) + img * 2 * px : nullptr;
   J.x = A.x ? reinterpret_cast<float2*>(A.x) + img * px : nullptr;
   J.m = A.m;
@@ -612,7 +708,22 @@ __global__ __launch_bounds__(kSingleNW * 64) void fgp_single_kernel(FgpSingleArg
   J.T = A.T;
   J.r_hist = nullptr;
   J.hist_stride = 0;
-  fgp_tile_col<KIND, CONSTR, MASK, kSingleNW, kSingleP, true>(J, 0, sBeta, sRows);
+}
+
+template <int KIND, int CONSTR, bool MASK>
+__global__ __launch_bounds__(kSingleNW * 64) void fgp_single_kernel(FgpSingleArgs A) {
+  __shared__ float2 sRows[2 * (kSingleNW + 1) * kRW];
+  __shared__ int sOdd;
+  __shared__ float sBeta[kFlowMaxIters];
+  for (int i = threadIdx.x; i < A.T; i += blockDim.x) sBeta[i] = A.beta[i];
+  if (threadIdx.x == 0) sOdd = 0;
+  __syncthreads();
+  TileJob J;
+  single_job(A, J);
+  if (opaque(fgp_tile_col<KIND, CONSTR, MASK, kSingleNW, kSingleP, true, false, false, true>(J, 0, sBeta, sRows, &sOdd)))
+    return;
+  single_job(args_again<FgpSingleArgs>(), J);
+  fgp_tile_col<KIND, CONSTR, MASK, kSingleNW, kSingleP, true, false, false, false>(J, 0, sBeta, sRows, &sOdd);
 }
 
 // ---------------------------------------------------------------------------
@@ -647,7 +758,7 @@ __global__ __launch_bounds__(kThreads) void fgp_plain_kernel(FgpPlainArgs P) {
   J.T = P.T;
   J.r_hist = nullptr;
   J.hist_stride = 0;
-  fgp_tile<KIND, CONSTR, MASK, RH>(J, P.halo, sBeta, sA1, sA2, sY);
+  fgp_tile_lds<KIND, CONSTR, MASK, RH>(J, P.halo, sBeta, sA1, sA2, sY);
 }
 
 // ---------------------------------------------------------------------------
@@ -661,27 +772,22 @@ __global__ __launch_bounds__(kThreads) void fgp_plain_kernel(FgpPlainArgs P) {
 // workgroup runs one tile: a loop over tiles kept enough alive across the switch
 // to spill 71 registers of the 16 x 4 tile.
 // ---------------------------------------------------------------------------
-template <int CONSTR, int NW, int P>
-__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NW, P)))) void fgp_batched_kernel(FgpBatchedArgs A) {
-  __shared__ float2 sRows[2 * (NW + 1) * kRW];
-  __shared__ float sBeta[kMaxFuse];
-  if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = (threadIdx.x < A.T) ? A.beta_table[A.k0 + 1 + threadIdx.x] : 0.0f;
-  __syncthreads();
+__device__ __forceinline__ bool batched_job(const FgpBatchedArgs& A, TileJob& J, int& H) {
   constexpr int kXcd = 8;
   const int xcd = blockIdx.x % kXcd, bi = blockIdx.x / kXcd;
   const int nrun = A.live ? A.live_count[0] : A.ntiles;  // <= gridDim.x
   const int each = nrun / kXcd, rem = nrun % kXcd;
-  if (bi >= each + (xcd < rem ? 1 : 0)) return;
+  if (bi >= each + (xcd < rem ? 1 : 0)) return false;
   const int t = xcd * each + min(xcd, rem) + bi;
   const BatchTile bt = A.tiles[A.live ? A.live[t] : t];
   const BatchImage D = A.images[bt.image];
   const int Ti = min(A.T, D.iters - A.k0);
   const bool last = (A.k0 + Ti == D.iters);
-  const int H = max(1, Ti + (last ? 1 : 0));
-  TileJob J;
+  H = max(1, Ti + (last ? 1 : 0));
   J.b = reinterpret_cast<const float2*>(A.b) + D.offset;
   J.mask = (D.support_offset >= 0 && A.support) ? A.support + D.support_offset : nullptr;
   J.st_in = (A.k0 == 0) ? nullptr : reinterpret_cast<const float4*>(A.st_in) + 2 * D.offset;
+  J.foreign = false;
   J.st_out = last ? nullptr : reinterpret_cast<float4*>(A.st_out) + 2 * D.offset;
   J.x = last ? reinterpret_cast<float2*>(A.x) + D.offset : nullptr;
   J.m = D.m;
@@ -694,21 +800,35 @@ __global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_p
   J.T = Ti;
   J.r_hist = nullptr;
   J.hist_stride = 0;
-  const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (NW * P - 2 * H) - H;
-  const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + NW * P <= J.m - 1;
-  const int sel = (D.kind * 2 + (J.mask ? 1 : 0)) * 2 + (interior ? 0 : 1);
-  switch (sel) {
-#define CTV_B(KI, MK, BO, S)                                     \
-  case S:                                                        \
-    fgp_tile_col<KI, CONSTR, MK, NW, P, BO>(J, H, sBeta, sRows); \
+  J.kind = D.kind;
+  return true;
+}
+
+template <int CONSTR, int NW, int P>
+__global__ __launch_bounds__(NW * 64) __attribute__((amdgpu_waves_per_eu(waves_per_simd(NW, P)))) void fgp_batched_kernel(FgpBatchedArgs A) {
+  __shared__ float2 sRows[2 * (NW + 1) * kRW];
+  __shared__ int sOdd;
+  __shared__ float sBeta[kMaxFuse];
+  if (threadIdx.x < kMaxFuse) sBeta[threadIdx.x] = (threadIdx.x < A.T) ? A.beta_table[A.k0 + 1 + threadIdx.x] : 0.0f;
+  if (threadIdx.x == 0) sOdd = 0;
+  __syncthreads();
+  TileJob J;
+  int H;
+  if (!batched_job(A, J, H)) return;
+  int done;
+  switch (J.kind * 2 + (J.mask ? 1 : 0)) {
+#define CTV_B(KI, MK, S)                                                  \
+  case S:                                                                 \
+    done = finite_tile<KI, CONSTR, MK, NW, P>(J, H, sBeta, sRows, &sOdd); \
     break;
-    CTV_B(K1I, false, false, 0) CTV_B(K1I, false, true, 1) CTV_B(K1I, true, false, 2) CTV_B(K1I, true, true, 3)
-    CTV_B(K1A, false, false, 4) CTV_B(K1A, false, true, 5) CTV_B(K1A, true, false, 6) CTV_B(K1A, true, true, 7)
-    CTV_B(K2I, false, false, 8) CTV_B(K2I, false, true, 9) CTV_B(K2I, true, false, 10) CTV_B(K2I, true, true, 11)
-    CTV_B(K2A, false, false, 12) CTV_B(K2A, false, true, 13) CTV_B(K2A, true, false, 14)
-    default: fgp_tile_col<K2A, CONSTR, true, NW, P, true>(J, H, sBeta, sRows); break;
+    CTV_B(K1I, false, 0) CTV_B(K1I, true, 1) CTV_B(K1A, false, 2) CTV_B(K1A, true, 3)
+    CTV_B(K2I, false, 4) CTV_B(K2I, true, 5) CTV_B(K2A, false, 6)
+    default: done = finite_tile<K2A, CONSTR, true, NW, P>(J, H, sBeta, sRows, &sOdd); break;
 #undef CTV_B
   }
+  if (opaque(done)) return;
+  batched_job(args_again<FgpBatchedArgs>(), J, H);
+  fgp_tile_col<kAnyKind, CONSTR, true, NW, P, true, false, false, false>(J, H, sBeta, sRows, &sOdd);
 }
 
 // ---------------------------------------------------------------------------
