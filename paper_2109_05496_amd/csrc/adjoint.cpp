@@ -217,6 +217,7 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
           a.beta[i] = (i < steps && k >= 2) ? beta[(size_t)(k - 1)] : 0.0f;
         }
         a.steps = steps;
+        a.saved_step = (ck && khi - steps == ks) ? steps - 1 : -1;
         a.adj_in = cur;
         a.adj_out = (khi - steps + 1 == 1) ? nullptr : nxt;
         a.live = live;

@@ -25,6 +25,7 @@ struct AdjStepArgs {
   int halo;                 // tile halo, >= steps + 1: one for all reverse steps of a call, another for the output step
   int b_zero;               // reverse step: plane B of adj_in is zero and is not read
   int steps;                // reverse steps in this launch, 1..kMaxRev
+  int saved_step;           // the step whose r is the caller's checkpoint, or -1
   float beta[kMaxRev];      // beta_{k-1} of each fused step k
   Radii R;
   float lam[kPlainChunk];

@@ -71,6 +71,24 @@ __device__ __forceinline__ void buf_st2(__amdgpu_buffer_rsrc_t r, int off, float
   __builtin_amdgcn_raw_buffer_store_b64(u, r, off, 0, AUX);
 }
 
+// A tile kernel runs its form for finite values first (FIN = true) and, where that
+// returns false, the form for any value, behind a condition that the compiler cannot
+// look through and with the job read again from the kernel's arguments: otherwise it
+// places the second form before the loop of the first and keeps the first's registers
+// through it (63 -> 102 of the forward 8 x 4 tile), or keeps the job in scalar registers
+// that the first form spills (16 x 4: 2-3 % of a masked launch).
+__device__ __forceinline__ bool opaque(int done) {
+  done = __builtin_amdgcn_readfirstlane(done);
+  asm volatile("" : "+s"(done) : : "memory");
+  return __builtin_expect(done != 0, 1);
+}
+template <class A>
+__device__ __forceinline__ const A& args_again() {  // of a kernel whose only argument is an A
+  auto p = __builtin_amdgcn_kernarg_segment_ptr();
+  asm volatile("" : "+s"(p));
+  return *(const A*)p;
+}
+
 // Bits [max(a, 0), min(b, n)) set: the rows i of a wave with a <= i < b. a and b
 // are the same in every lane; readfirstlane between the two bounds
 // keeps them scalar (the compiler makes a vector median of them otherwise).

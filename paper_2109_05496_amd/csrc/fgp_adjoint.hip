@@ -33,12 +33,16 @@ namespace ctv {
 
 namespace {
 
+// Largest |A|, |B| and |w| of the form of the reverse step for finite values: with a
+// dual step of at most 1.25e11 no product of them leaves float32.
+constexpr float kGradRange = 1e12f;
+
 // Same operations as proj_c, also returning the scale s (1 when inactive).
-template <int CONSTR>
+template <int CONSTR, bool FIN>
 __device__ __forceinline__ float2 proj_c_s(float2 w, bool inside, float& s) {
   if (CONSTR == C_MOD) {
     const float n2 = fmaf(w.x, w.x, w.y * w.y);
-    s = unit_scale<true>(rsq(n2));
+    s = unit_scale<FIN>(rsq(n2));
     const float sm = inside ? s : 0.0f;
     return make_float2(fmaf(w.x, sm, 0.0f), fmaf(w.y, sm, 0.0f));
   }
@@ -47,16 +51,17 @@ __device__ __forceinline__ float2 proj_c_s(float2 w, bool inside, float& s) {
 }
 
 // J_PC(w)^T ybar.
-template <int CONSTR>
+template <int CONSTR, bool FIN>
 __device__ __forceinline__ float2 proj_c_vjp(float2 w, float s, bool inside, float2 yb) {
   float2 o = yb;
   if (CONSTR == C_MOD) {
-    // s (I - w w^T s^2) yb with s = 1/|w|; without the rank-one term (d = 0) where
-    // the projection is inactive (s = 1), which leaves yb. No branch: it would
-    // be taken by some lane of nearly every wave.
+    // s (I - w w^T s^2) yb with s = 1/|w|; yb where the projection is inactive (s = 1):
+    // there the rank-one term is dropped (d = 0), which leaves yb if w is finite. No
+    // branch: it would be taken by some lane of nearly every wave.
     const float t = fmaf(w.x, yb.x, w.y * yb.y) * (s * s);
     const float d = s < 1.0f ? t : 0.0f;
-    o = make_float2(s * fmaf(-w.x, d, yb.x), s * fmaf(-w.y, d, yb.y));
+    const float2 v = make_float2(s * fmaf(-w.x, d, yb.x), s * fmaf(-w.y, d, yb.y));
+    if (FIN || s < 1.0f) o = v;
   }
   return inside ? o : make_float2(0.0f, 0.0f);
 }
@@ -78,23 +83,24 @@ __device__ __forceinline__ void ball_vjp2(float vx, float vy, float ax, float ay
   }
 }
 
-template <int KIND>
+template <int KIND, bool FIN>
 __device__ __forceinline__ float4 proj_s_vjp(float4 g, float4 a, const Radii& R) {
   float4 o;
   if (KIND == K1I) {
     const float n2 = fmaf(g.x, g.x, fmaf(g.y, g.y, fmaf(g.z, g.z, g.w * g.w)));
-    const float s = unit_scale<true>(rsq(n2));
+    const float s = unit_scale<FIN>(rsq(n2));
     const float t = fmaf(g.x, a.x, fmaf(g.y, a.y, fmaf(g.z, a.z, g.w * a.w))) * (s * s);
     const float d = s < 1.0f ? t : 0.0f;  // inactive: o = a
     o = make_float4(s * fmaf(-g.x, d, a.x), s * fmaf(-g.y, d, a.y), s * fmaf(-g.z, d, a.z), s * fmaf(-g.w, d, a.w));
+    if (!FIN && !(s < 1.0f)) o = a;
   } else if (KIND == K1A) {
-    const float s1 = unit_scale<true>(rsq(fmaf(g.x, g.x, g.y * g.y)));
-    const float s2 = unit_scale<true>(rsq(fmaf(g.z, g.z, g.w * g.w)));
+    const float s1 = unit_scale<FIN>(rsq(fmaf(g.x, g.x, g.y * g.y)));
+    const float s2 = unit_scale<FIN>(rsq(fmaf(g.z, g.z, g.w * g.w)));
     ball_vjp2(g.x, g.y, a.x, a.y, s1, 1.0f, o.x, o.y);
     ball_vjp2(g.z, g.w, a.z, a.w, s2, 1.0f, o.z, o.w);
   } else if (KIND == K2I) {
-    const float fr = ball_scale<true>(R.ra, fmaf(g.x, g.x, g.z * g.z));
-    const float fs = ball_scale<true>(R.sa, fmaf(g.y, g.y, g.w * g.w));
+    const float fr = ball_scale<FIN>(R.ra, fmaf(g.x, g.x, g.z * g.z));
+    const float fs = ball_scale<FIN>(R.sa, fmaf(g.y, g.y, g.w * g.w));
     ball_vjp2(g.x, g.z, a.x, a.z, fr, R.ra, o.x, o.z);
     ball_vjp2(g.y, g.w, a.y, a.w, fs, R.sa, o.y, o.w);
   } else {
@@ -104,6 +110,12 @@ __device__ __forceinline__ float4 proj_s_vjp(float4 g, float4 a, const Radii& R)
     o.w = (R.sa > 0.0f && fabsf(g.w) <= R.sa) ? a.w : 0.0f;
   }
   return o;
+}
+
+// Zero in the entries of a pixel's dual that do not exist.
+__device__ __forceinline__ void keep_existing(bool has_down, bool has_right, float4& v) {
+  if (!has_down) v.x = v.y = 0.0f;
+  if (!has_right) v.z = v.w = 0.0f;
 }
 
 struct AdjJob {
@@ -119,6 +131,7 @@ struct AdjJob {
   double* lam_acc;           // per-tile accumulator slot
   int m, n, tx, ty;
   int steps;                 // reverse steps fused in this launch
+  int saved_step;            // the step whose r is a caller's checkpoint, or -1
   bool b_zero;               // B is zero and was not stored (first launch after the output step)
   float lam, c, cc;          // lambda, 1/(8 lambda), 1/(8 lambda^2)
   float beta[kMaxRev];       // beta_{k-1} of each fused step
@@ -157,9 +170,16 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
 // the running bbar (started from grad_b, so the sum is taken in the same order
 // as one step per launch) stay in registers between steps and are stored once,
 // for the tile's output pixels.
-template <int KIND, int CONSTR, bool MASK, int NW, int P, bool BORDER>
-__device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* sX1, float2* sX2, float2* sX3,
-                                         float2* sX4, double* red) {
+//
+// FIN = true is the step for finite values: scales through the clamp modifier, zero
+// steps. It returns false, with nothing stored, where an A, B or w of the region is not
+// finite or too large to stay so, or a checkpoint holds a dual where none exists (2
+// operations a pixel and step: 3497 -> 3520 us for the forward and backward pass of 16 x
+// 512^2). FIN = false (with BORDER = true: it takes any tile) selects instead, so a value
+// that is not finite reaches no gradient through a dual that does not exist.
+template <int KIND, int CONSTR, bool MASK, int NW, int P, bool BORDER, bool FIN>
+__device__ __forceinline__ bool adj_tile(const AdjJob& J, const int H, float2* sX1, float2* sX2, float2* sX3,
+                                         float2* sX4, double* red, int* sOdd) {
   constexpr int RH = NW * P;
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
@@ -226,6 +246,15 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
     }
   }
   load_r(J.r[0]);
+  float mag = 0.0f;
+  unsigned extra = 0;
+  if (FIN) {
+    if (threadIdx.x == 0) *sOdd = 0;
+#pragma unroll
+    for (int i = 0; i < P; ++i)
+      mag += ((fabsf(A[i].x) + fabsf(A[i].y)) + (fabsf(A[i].z) + fabsf(A[i].w))) +
+             ((fabsf(B[i].x) + fabsf(B[i].y)) + (fabsf(B[i].z) + fabsf(B[i].w)));
+  }
   double lam_part = 0.0;  // of the lane's column in the tile's output rows; other lanes' sums are dropped
 
 #pragma unroll
@@ -245,8 +274,19 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
         const float2 up = (i > 0) ? make_float2(r[i - 1].x, r[i - 1].y) : up0;
         dd[i] = make_float2((r[i].x - up.x) + (r[i].z - lx), (r[i].y - up.y) + (r[i].w - ly));
         w[i] = make_float2(fmaf(-lam, dd[i].x, b[i].x), fmaf(-lam, dd[i].y, b[i].y));
-        y[i] = proj_c_s<CONSTR>(w[i], inside[i], s[i]);
+        y[i] = proj_c_s<CONSTR, FIN>(w[i], inside[i], s[i]);
+        if (FIN) mag += fabsf(w[i].x) + fabsf(w[i].y);
       }
+    }
+    if (FIN) {
+      if (BORDER && st == J.saved_step) {
+#pragma unroll
+        for (int i = 0; i < P; ++i) {
+          if (!has_down(jb + i)) extra |= __float_as_uint(r[i].x) | __float_as_uint(r[i].y);
+          if (!has_right) extra |= __float_as_uint(r[i].z) | __float_as_uint(r[i].w);
+        }
+      }
+      if (st + 1 == J.steps && __builtin_amdgcn_ballot_w64(!(mag < kGradRange) || extra != 0)) *sOdd = 1;
     }
     // stage 2: g from y (down / right); gbar = J_PS^T A
     sX2[wave * kRW + lane] = y[0];
@@ -260,10 +300,16 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
         const float cv = has_down(jb + i) ? c : 0.0f;
         const float rx = lane_from_right(y[i].x), ry = lane_from_right(y[i].y);
         const float2 down = (i < P - 1) ? y[i + 1] : down_last;
-        const float l1x = y[i].x - down.x, l1y = y[i].y - down.y, l2x = y[i].x - rx, l2y = y[i].y - ry;
-        const float4 g = make_float4(fmaf(cv, l1x, r[i].x), fmaf(cv, l1y, r[i].y), fmaf(ch, l2x, r[i].z),
-                                     fmaf(ch, l2y, r[i].w));
-        const float4 gb = proj_s_vjp<KIND>(g, A[i], R);
+        float l1x = y[i].x - down.x, l1y = y[i].y - down.y, l2x = y[i].x - rx, l2y = y[i].y - ry;
+        float4 g = make_float4(fmaf(cv, l1x, r[i].x), fmaf(cv, l1y, r[i].y), fmaf(ch, l2x, r[i].z),
+                               fmaf(ch, l2y, r[i].w));
+        if (!FIN) {
+          keep_existing(has_down(jb + i), has_right, g);
+          if (!has_down(jb + i)) l1x = l1y = 0.0f;
+          if (!has_right) l2x = l2y = 0.0f;
+        }
+        float4 gb = proj_s_vjp<KIND, FIN>(g, A[i], R);
+        if (!FIN) keep_existing(has_down(jb + i), has_right, gb);
         gbar[i] = gb;
         if (row_out(i)) {
           asm volatile("");
@@ -286,7 +332,7 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
         const float2 up = (i > 0) ? make_float2(gbar[i - 1].x, gbar[i - 1].y) : up0;
         const float2 yb = make_float2(c * ((gbar[i].x - up.x) + (gbar[i].z - lx)),
                                       c * ((gbar[i].y - up.y) + (gbar[i].w - ly)));
-        wbar[i] = proj_c_vjp<CONSTR>(w[i], s[i], inside[i], yb);
+        wbar[i] = proj_c_vjp<CONSTR, FIN>(w[i], s[i], inside[i], yb);
         bacc[i] = make_float2(bacc[i].x + wbar[i].x, bacc[i].y + wbar[i].y);
         if (row_out(i)) {
           asm volatile("");
@@ -307,14 +353,16 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
         const float lv = has_down(jb + i) ? lam : 0.0f;
         const float rx = lane_from_right(wbar[i].x), rv = lane_from_right(wbar[i].y);
         const float2 down = (i < P - 1) ? wbar[i + 1] : down_last;
-        const float4 rb = make_float4(fmaf(-lv, wbar[i].x - down.x, gbar[i].x), fmaf(-lv, wbar[i].y - down.y, gbar[i].y),
-                                      fmaf(-lh, wbar[i].x - rx, gbar[i].z), fmaf(-lh, wbar[i].y - rv, gbar[i].w));
+        float4 rb = make_float4(fmaf(-lv, wbar[i].x - down.x, gbar[i].x), fmaf(-lv, wbar[i].y - down.y, gbar[i].y),
+                                fmaf(-lh, wbar[i].x - rx, gbar[i].z), fmaf(-lh, wbar[i].y - rv, gbar[i].w));
+        if (!FIN) keep_existing(has_down(jb + i), has_right, rb);
         A[i] = make_float4(fmaf(a1, rb.x, B[i].x), fmaf(a1, rb.y, B[i].y), fmaf(a1, rb.z, B[i].z),
                            fmaf(a1, rb.w, B[i].w));
         B[i] = make_float4(nbeta * rb.x, nbeta * rb.y, nbeta * rb.z, nbeta * rb.w);
       }
     }
   }
+  if (FIN && __builtin_amdgcn_readfirstlane(*sOdd)) return false;
 #pragma unroll
   for (int i = 0; i < P; ++i) {
     const int j = jb + i;
@@ -338,6 +386,7 @@ __device__ __forceinline__ void adj_tile(const AdjJob& J, const int H, float2* s
   }
   const double tot = block_sum_d(col_out ? lam_part : 0.0, red);
   if (threadIdx.x == 0) *J.lam_acc += tot;
+  return true;
 }
 
 // Output step: w = b - lambda L^T q_K, wbar = J_PC(w)^T xbar, bbar = wbar,
@@ -400,8 +449,8 @@ __device__ __forceinline__ void adj_out_tile(const AdjJob& J, const int H, const
       const float2 d = make_float2((q[i].x - up.x) + (q[i].z - left.x), (q[i].y - up.y) + (q[i].w - left.y));
       const float2 w = dual_to_primal(b[i], q[i], up, left, J.lam);
       float s;
-      (void)proj_c_s<CONSTR>(w, inside[i], s);
-      wbar[i] = proj_c_vjp<CONSTR>(w, s, inside[i], xb[i]);
+      (void)proj_c_s<CONSTR, false>(w, inside[i], s);
+      wbar[i] = proj_c_vjp<CONSTR, false>(w, s, inside[i], xb[i]);
       const int ry = wave * P + i;
       if (ry >= H && ry < RH - H && lane >= H && lane < kRW - H && in[i])
         lam_part += (double)(-(wbar[i].x * d.x + wbar[i].y * d.y));
@@ -474,15 +523,9 @@ __device__ __forceinline__ bool adj_job_common(const AdjStepArgs& A, int& img, A
   return true;
 }
 
-// Occupancy pinned at 4 waves per SIMD: left free, the type-1a and type-2i
-// variants with the modulus bound take a few registers more and drop to 3.
-template <int KIND, int CONSTR, bool MASK>
-__global__ __launch_bounds__(kNW * 64) __attribute__((amdgpu_waves_per_eu(4))) void adj_step_kernel(AdjStepArgs A) {
-  __shared__ float2 sX1[kNW * kRW], sX2[kNW * kRW], sX3[kNW * kRW], sX4[kNW * kRW];
-  __shared__ double red[kNW];
+__device__ __forceinline__ bool adj_step_job(const AdjStepArgs& A, AdjJob& J) {
   int img;
-  AdjJob J;
-  if (!adj_job_common(A, img, J)) return;
+  if (!adj_job_common(A, img, J)) return false;
   const long long px = (long long)A.m * A.n;
   // plane 1 (r) of each step's state
   auto rplane = [&](const float* r) { return r ? reinterpret_cast<const float4*>(r) + img * 2 * px + px : nullptr; };
@@ -491,14 +534,32 @@ __global__ __launch_bounds__(kNW * 64) __attribute__((amdgpu_waves_per_eu(4))) v
     J.r[st] = rplane(A.r[st]);
     J.beta[st] = A.beta[st];
   }
+  J.saved_step = A.saved_step;
   J.adj_in = reinterpret_cast<const float4*>(A.adj_in) + img * 2 * px;
+  return true;
+}
+
+// Occupancy pinned at 4 waves per SIMD: left free, the type-1a and type-2i
+// variants with the modulus bound take a few registers more and drop to 3.
+template <int KIND, int CONSTR, bool MASK>
+__global__ __launch_bounds__(kNW * 64) __attribute__((amdgpu_waves_per_eu(4))) void adj_step_kernel(AdjStepArgs A) {
+  __shared__ float2 sX1[kNW * kRW], sX2[kNW * kRW], sX3[kNW * kRW], sX4[kNW * kRW];
+  __shared__ double red[kNW];
+  __shared__ int sOdd;
+  AdjJob J;
+  if (!adj_step_job(A, J)) return;
   const int H = A.halo;
   const int c0 = J.tx * (kRW - 2 * H) - H, r0 = J.ty * (kNW * kP - 2 * H) - H;
   const bool interior = c0 >= 1 && c0 + kRW <= J.n - 1 && r0 >= 1 && r0 + kNW * kP <= J.m - 1;
+  int done;
   if (interior)
-    adj_tile<KIND, CONSTR, MASK, kNW, kP, false>(J, H, sX1, sX2, sX3, sX4, red);
+    done = adj_tile<KIND, CONSTR, MASK, kNW, kP, false, true>(J, H, sX1, sX2, sX3, sX4, red, &sOdd);
   else
-    adj_tile<KIND, CONSTR, MASK, kNW, kP, true>(J, H, sX1, sX2, sX3, sX4, red);
+    done = adj_tile<KIND, CONSTR, MASK, kNW, kP, true, true>(J, H, sX1, sX2, sX3, sX4, red, &sOdd);
+  if (opaque(done)) return;
+  const AdjStepArgs& again = args_again<AdjStepArgs>();
+  adj_step_job(again, J);
+  adj_tile<KIND, CONSTR, MASK, kNW, kP, true, false>(J, again.halo, sX1, sX2, sX3, sX4, red, &sOdd);
 }
 
 template <int CONSTR, bool MASK>
@@ -531,8 +592,8 @@ __global__ __launch_bounds__(256) void pc_vjp_kernel(const float2* __restrict__ 
   if (i >= total) return;
   const bool in = mask ? (mask[i % px] != 0) : true;
   float s;
-  (void)proj_c_s<CONSTR>(b[i], in, s);
-  gb[i] = proj_c_vjp<CONSTR>(b[i], s, in, xbar[i]);
+  (void)proj_c_s<CONSTR, false>(b[i], in, s);
+  gb[i] = proj_c_vjp<CONSTR, false>(b[i], s, in, xbar[i]);
 }
 
 // One wave per image: lane l sums the tiles l, l + 64, ... in order, then the

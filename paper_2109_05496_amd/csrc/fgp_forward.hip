@@ -475,23 +475,6 @@ __device__ __forceinline__ int finite_tile(const TileJob& J, const int H, const 
   return fgp_tile_col<KIND, CONSTR, MASK, NW, P, true, HIST, COH, true>(J, H, sBeta, sRows, sOdd);
 }
 
-// The FIN = false form follows in the same kernel, behind a value that the compiler
-// cannot look through and with the job read again from the kernel's arguments:
-// otherwise it places the second form before the loop of the first and keeps the
-// first's registers through it (63 -> 102 of the 8 x 4 tile), or keeps the job in
-// scalar registers that the first form spills (16 x 4: 2-3 % of a masked launch).
-__device__ __forceinline__ bool opaque(int done) {
-  done = __builtin_amdgcn_readfirstlane(done);
-  asm volatile("" : "+s"(done) : : "memory");
-  return __builtin_expect(done != 0, 1);
-}
-template <class A>
-__device__ __forceinline__ const A& args_again() {  // of a kernel whose only argument is an A
-  auto p = __builtin_amdgcn_kernarg_segment_ptr();
-  asm volatile("" : "+s"(p));
-  return *(const A*)p;
-}
-
 // The tile of this workgroup; false if it has none (live-tile list shorter than the grid).
 template <bool HIST>
 __device__ __forceinline__ bool plain_job(const FgpPlainArgs& P_, TileJob& J) {
