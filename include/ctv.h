@@ -120,6 +120,12 @@ const char* ctv_last_error(void);
  * state_out) come back NaN. on = 0 restores normal runs. Always CTV_OK. */
 ctv_status ctv_debug_flow_fail_waits(int32_t on);
 
+/* Test hook: the tiling that ctv_denoise chooses for these parameters with
+ * checkpoints every ckpt_every iterations (0 = none) on a device with `cus`
+ * compute units (0 = the current device's). Nothing is launched. */
+ctv_status ctv_debug_tiling(const ctv_params* p, int32_t batch, int32_t m, int32_t n, int32_t ckpt_every, int32_t cus,
+                            int32_t* fuse_out, int32_t* tile_waves_out, int32_t* tile_rows_out);
+
 /* Workspace (and checkpoint storage) needed by ctv_denoise /
  * ctv_denoise_backward for `batch` images of m x n.
  *   ws_bytes    : scratch for ctv_denoise; ctv_denoise_backward needs
@@ -130,9 +136,12 @@ ctv_status ctv_debug_flow_fail_waits(int32_t on);
 ctv_status ctv_workspace_size(const ctv_params* p, int32_t batch, int32_t m, int32_t n,
                               int32_t ckpt_every, size_t* ws_bytes, size_t* saved_bytes);
 
-/* Launch configuration ctv_denoise uses for these sizes: iterations fused per
- * kernel launch, tile region rows (tiles are 64 columns wide) and the tile
- * shape in ctv_params' tile_waves / tile_rows terms. Host-only; any output
+/* Launch configuration ctv_denoise uses for these sizes without checkpoints:
+ * iterations fused per kernel launch, tile region rows (tiles are 64 columns
+ * wide) and the tile shape in ctv_params' tile_waves / tile_rows terms. Nothing
+ * is launched; the automatic choice asks the current device for its number of
+ * compute units. Without a device it is that of a whole MI355X (256), but for
+ * the 64 x 64 region's form, which is then reported as 8 x 8. Any output
  * pointer may be NULL.
  * Fails with CTV_ERR_INVALID_ARG for an unsupported tile_waves/tile_rows pair. */
 ctv_status ctv_tiling(const ctv_params* p, int32_t batch, int32_t m, int32_t n, int32_t* fuse_out,

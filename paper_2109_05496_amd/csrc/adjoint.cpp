@@ -113,7 +113,7 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
   tp.tile_waves = 0;
   tp.tile_rows = 0;
   tp.iters = c;
-  st = choose_tiling(&tp, m, n, batch, &tl);
+  st = choose_tiling(&tp, m, n, batch, 0, &tl);
   if (st) return st;
   tl.shape.waves = 16;  // the form of the 64 x 64 region that stores the history
   tl.shape.rows_per_thread = 4;

@@ -211,7 +211,7 @@ ctv_status ctv_batched_plan_create(const ctv_image_desc* descs, int32_t count, c
   Tiling tl;
   ctv_params tp = *common;
   tp.iters = std::max(kmax, 1);
-  st = choose_tiling(&tp, 1, 1, count, &tl);
+  st = choose_tiling(&tp, 1, 1, count, 0, &tl);
   if (st) return st;
   if (common->fuse == 0 && common->tile_waves == 0 && common->tile_rows == 0) {
     Tiling tuned;
@@ -223,7 +223,7 @@ ctv_status ctv_batched_plan_create(const ctv_image_desc* descs, int32_t count, c
       const long long o = 64 - 2 * std::max(1, tl.T);
       long long tiles = 0;
       for (const BatchImage& d : imgs) tiles += ((d.n + o - 1) / o) * ((d.m + o - 1) / o);
-      if (region_as_16x4(tiles)) tl.shape.waves = 16, tl.shape.rows_per_thread = 4;
+      if (region_as_16x4(tiles, device_cus())) tl.shape.waves = 16, tl.shape.rows_per_thread = 4;
     }
   }
   ctv_batched_plan* p = new ctv_batched_plan();

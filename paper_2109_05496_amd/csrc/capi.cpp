@@ -108,21 +108,25 @@ void clamp_fuse(Tiling* t, int iters) {
   t->T = std::max(t->T, 1);
 }
 
+// Compute units of the current device; 0 without one (nothing can be launched). Not
+// kept: a process may change its device, and the two queries take no measurable time.
+int device_cus() {
+  int dev = 0, cus = 0;
+  if (hipGetDevice(&dev) != hipSuccess ||
+      hipDeviceGetAttribute(&cus, hipDeviceAttributeMultiprocessorCount, dev) != hipSuccess) {
+    (void)hipGetLastError();
+    return 0;
+  }
+  return cus;
+}
+
 // The automatic 64 x 64 region runs as 16 waves x 4 rows where it has more tiles
 // than CUs: two workgroups share a CU at 8 waves per SIMD, where the 8 x 8 form
 // has 4. Measured 8 x 8 -> 16 x 4, T = 8: 700^2 .. 8192^2, all kinds, -3 .. -8 %,
 // plans of 4 x 2048^2 2543 -> 2402 us, 64 images of 128 .. 1024 a side 3202 -> 3110.
 // With one tile per CU the two are within 4 % (small_tiling's costs). Without a
-// device (nothing can be launched) the plain default is reported.
-bool region_as_16x4(long long tiles) {
-  if (tiles <= 256) return false;
-  int devices = 0;
-  if (hipGetDeviceCount(&devices) != hipSuccess) {
-    (void)hipGetLastError();
-    return false;
-  }
-  return devices > 0;
-}
+// device (cus = 0) the plain default is reported.
+bool region_as_16x4(long long tiles, int cus) { return cus > 0 && tiles > cus; }
 
 // Tile shape and fusion depth for a run of `iters` iterations where one or two
 // tiles per CU cover the problem. A launch's time is then not bandwidth but the latency of
@@ -137,7 +141,7 @@ bool region_as_16x4(long long tiles) {
 // 3.13 -> 2.61, 960^2 3.20 -> 2.80. With more
 // tiles per CU the shapes differ by less than the model's error (1000 x 1501 chosen
 // by it: 293 -> 326 us), so the line is drawn there.
-static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
+static void small_tiling(int m, int n, int batch, int iters, int cus, Tiling* out) {
   struct Cost {
     int waves, rows, per_cu;
     double fixed, step;
@@ -145,12 +149,13 @@ static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
   static const Cost costs[] = {{8, 8, 1, 6.5, 1.20}, {12, 4, 1, 5.5, 0.92},  {8, 4, 1, 4.7, 0.81},
                                {16, 4, 1, 7.2, 1.05}, {12, 4, 2, 12.4, 1.03}, {8, 4, 2, 6.5, 1.10},
                                {16, 4, 2, 8.7, 1.93}};
-  constexpr int kCus = 256, kMaxT = 14;
+  constexpr int kMaxT = 14;
+  if (cus <= 0) cus = 256;  // without a device, as on a whole MI355X
   const int images = std::min(batch, kPlainChunk);
   const double px = (double)m * n * images;
   auto per_cu = [&](const Cost& c, int T) {
     const long long ow = 64 - 2 * T, oh = c.waves * c.rows - 2 * T;
-    return (((n + ow - 1) / ow) * ((m + oh - 1) / oh) * images + kCus - 1) / kCus;
+    return (((n + ow - 1) / ow) * ((m + oh - 1) / oh) * images + cus - 1) / cus;
   };
   auto launches = [&](int T) { return (iters + T - 1) / T; };
   const long long k = iters > 0 ? per_cu(costs[0], std::min(8, iters)) : 0;
@@ -176,7 +181,7 @@ static void small_tiling(int m, int n, int batch, int iters, Tiling* out) {
     }
 }
 
-ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* out, bool use_tuned, int run) {
+ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, int cus, Tiling* out, bool use_tuned, int run) {
   Tiling t;
   t.shape.waves = 8;
   t.shape.rows_per_thread = 8;
@@ -195,10 +200,10 @@ ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* o
       t = tuned;
     } else {
       const int iters = run > 0 ? std::min(run, p->iters) : p->iters;
-      small_tiling(m, n, batch, iters, &t);
+      small_tiling(m, n, batch, iters, cus, &t);
       const long long o = 64 - 2 * std::max(1, std::min(8, iters));
       if (t.shape.waves == 8 && t.shape.rows_per_thread == 8 &&
-          region_as_16x4(((n + o - 1) / o) * ((m + o - 1) / o) * std::min(batch, kPlainChunk))) {
+          region_as_16x4(((n + o - 1) / o) * ((m + o - 1) / o) * std::min(batch, kPlainChunk), cus)) {
         t.shape.waves = 16;
         t.shape.rows_per_thread = 4;
         // 9 to 11 iterations between checkpoints in one launch instead of two, each
@@ -294,6 +299,22 @@ ctv_status ctv_debug_flow_fail_waits(int32_t on) {
   return CTV_OK;
 }
 
+ctv_status ctv_debug_tiling(const ctv_params* p, int32_t batch, int32_t m, int32_t n, int32_t ckpt_every, int32_t cus,
+                            int32_t* fuse_out, int32_t* tile_waves_out, int32_t* tile_rows_out) {
+  ctv_status st = validate_params(p);
+  if (st) return st;
+  if (batch < 1 || m < 1 || n < 1) return fail(CTV_ERR_INVALID_ARG, "batch, m and n must be >= 1");
+  if (ckpt_every < 0 || cus < 0) return fail(CTV_ERR_INVALID_ARG, "ckpt_every and cus must be >= 0");
+  if (!fuse_out || !tile_waves_out || !tile_rows_out) return fail(CTV_ERR_INVALID_ARG, "NULL output pointer");
+  Tiling t;
+  st = choose_tiling(p, m, n, batch, cus ? cus : device_cus(), &t, p->schedule != CTV_S_FLOW, ckpt_every);
+  if (st) return st;
+  *fuse_out = t.T;
+  *tile_waves_out = (t.shape.waves > 0 || t.shape.sweep()) ? t.shape.waves : -1;
+  *tile_rows_out = t.shape.rows_per_thread;
+  return CTV_OK;
+}
+
 ctv_status ctv_workspace_size(const ctv_params* p, int32_t batch, int32_t m, int32_t n,
                               int32_t ckpt_every, size_t* ws_bytes, size_t* saved_bytes) {
   ctv_status st = validate_params(p);
@@ -315,7 +336,7 @@ ctv_status ctv_tiling(const ctv_params* p, int32_t batch, int32_t m, int32_t n, 
   if (st) return st;
   if (batch < 1 || m < 1 || n < 1) return fail(CTV_ERR_INVALID_ARG, "batch, m and n must be >= 1");
   Tiling t;
-  st = choose_tiling(p, m, n, batch, &t, p->schedule != CTV_S_FLOW);
+  st = choose_tiling(p, m, n, batch, device_cus(), &t, p->schedule != CTV_S_FLOW);
   if (st) return st;
   if (fuse_out) *fuse_out = t.T;
   if (region_rows_out) *region_rows_out = t.shape.rows();
@@ -362,7 +383,7 @@ ctv_status ctv_denoise(const ctv_params* p, int32_t batch, int32_t m, int32_t n,
       reinterpret_cast<char*>(flow_mem) +
       align_up((size_t)flow_ints(std::min(batch, kPlainChunk), m, n, flow_max_halo()) * 4));
   Tiling tl;
-  st = choose_tiling(p, m, n, batch, &tl, p->schedule != CTV_S_FLOW, ckpt_every);
+  st = choose_tiling(p, m, n, batch, device_cus(), &tl, p->schedule != CTV_S_FLOW, ckpt_every);
   if (st) return st;
   const bool flow_ok = ckpt_every == 0 && p->iters > 0 && tl.shape.waves == 8 && tl.shape.rows_per_thread == 8;
   if (p->schedule == CTV_S_FLOW && !flow_ok)

@@ -25,12 +25,15 @@ void momentum_table(int method, int kmax, std::vector<float>& beta);
 float step_of(float lam);
 // Launch configuration for a plain call: the explicit fuse / tile of p, else
 // (use_tuned) an entry recorded by ctv_autotune for this problem, else the
-// shape and depth its size asks for (small_tiling, region_as_16x4). run > 0: the
-// iterations between two checkpoints (a launch does not cross one).
-ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, Tiling* out, bool use_tuned = false,
+// shape and depth its size asks for on a device with `cus` compute units
+// (small_tiling, region_as_16x4). run > 0: the iterations between two checkpoints (a
+// launch does not cross one).
+ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, int cus, Tiling* out, bool use_tuned = false,
                          int run = 0);
+// Compute units of the current device, 0 without one.
+int device_cus();
 // Whether the automatic 64 x 64 region with this many tiles runs as 16 waves x 4 rows.
-bool region_as_16x4(long long tiles);
+bool region_as_16x4(long long tiles, int cus);
 // Limits the fusion depth to what the tile shape's halo and the run allow.
 void clamp_fuse(Tiling* t, int iters);
 // Tuning table (autotune.cpp): problem keys and lookup for the current device.
