@@ -128,7 +128,7 @@ int device_cus() {
 // device (cus = 0) the plain default is reported.
 bool region_as_16x4(long long tiles, int cus) { return cus > 0 && tiles > cus; }
 
-// Tile shape and fusion depth for a run of `iters` iterations where one or two
+// Tile shape and fusion depth for `run` iterations where one or two
 // tiles per CU cover the problem. A launch's time is then not bandwidth but the latency of
 // one tile, fixed + step T for T iterations (microseconds, fitted to launches of
 // T = 4 .. 14 on MI355X, within 6 %): smaller tiles start sooner and have fewer
@@ -141,7 +141,7 @@ bool region_as_16x4(long long tiles, int cus) { return cus > 0 && tiles > cus; }
 // 3.13 -> 2.61, 960^2 3.20 -> 2.80. With more
 // tiles per CU the shapes differ by less than the model's error (1000 x 1501 chosen
 // by it: 293 -> 326 us), so the line is drawn there.
-static void small_tiling(int m, int n, int batch, int iters, int cus, Tiling* out) {
+static void small_tiling(int m, int n, int batch, int run, int cus, Tiling* out) {
   struct Cost {
     int waves, rows, per_cu;
     double fixed, step;
@@ -150,6 +150,7 @@ static void small_tiling(int m, int n, int batch, int iters, int cus, Tiling* ou
                                {16, 4, 1, 7.2, 1.05}, {12, 4, 2, 12.4, 1.03}, {8, 4, 2, 6.5, 1.10},
                                {16, 4, 2, 8.7, 1.93}};
   constexpr int kMaxT = 14;
+  const long long iters = run;  // any int is accepted: sums of it with a depth need more
   if (cus <= 0) cus = 256;  // without a device, as on a whole MI355X
   const int images = std::min(batch, kPlainChunk);
   const double px = (double)m * n * images;
@@ -158,14 +159,14 @@ static void small_tiling(int m, int n, int batch, int iters, int cus, Tiling* ou
     return (((n + ow - 1) / ow) * ((m + oh - 1) / oh) * images + cus - 1) / cus;
   };
   auto launches = [&](int T) { return (iters + T - 1) / T; };
-  const long long k = iters > 0 ? per_cu(costs[0], std::min(8, iters)) : 0;
+  const long long k = iters > 0 ? per_cu(costs[0], std::min(8, run)) : 0;
   if (k < 1 || k > 3) return;
-  const int Td = (iters + launches(8) - 1) / launches(8);
+  const long long Td = (iters + launches(8) - 1) / launches(8);
   double best = launches(8) * (3.5 + 3.0 * k + Td * (0.35 + 0.85 * k)) * (k > 1 ? 0.95 : 1.0);
   // an image inside one 8 x 8 tile: the single-tile kernel's one launch
   if (m <= 64 && n <= 64) best = (iters + kFlowMaxIters - 1) / kFlowMaxIters * 5.0 + 1.18 * iters;
   for (const Cost& c : costs)
-    for (int T = 1; T <= std::min({kMaxT, iters, c.waves * c.rows / 2 - 2}); ++T) {
+    for (int T = 1; T <= std::min({kMaxT, run, c.waves * c.rows / 2 - 2}); ++T) {
       if ((iters + launches(T) - 1) / launches(T) != T || per_cu(c, T) > c.per_cu) continue;
       // two 16 x 4 tiles a CU: below 8 iterations a launch is the memory's 21-23 us
       if (c.rows * c.waves == 64 && c.per_cu == 2 && T < 8) continue;

@@ -51,3 +51,9 @@ def test_a_part_of_the_device():
                 assert region <= 2 * cus, (m, n, cus)
             elif region > 3 * cus:
                 assert (waves, rows) == (16, 4), (m, n, cus)
+
+
+@pytest.mark.parametrize("m,n", [(64, 64), (100, 100), (500, 500), (700, 700)])
+def test_as_many_iterations_as_an_int_holds(m, n):
+    assert choice(m, n, 2 ** 31 - 1) == choice(m, n, 2 ** 30)
+    assert choice(m, n, 2 ** 31 - 5, ckpt=2 ** 31 - 1) == choice(m, n, 2 ** 30)
