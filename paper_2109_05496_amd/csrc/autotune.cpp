@@ -280,7 +280,14 @@ ctv_status ctv_autotune(const ctv_params* p, int32_t batch, int32_t m, int32_t n
   st = check_common(s, reps);
   if (st) return st;
   // the first candidate's call validates every other argument before any timing
-  const std::vector<Candidate> cands = candidates(false, p->iters, m <= 64 && n <= 64);
+  std::vector<Candidate> cands = candidates(false, p->iters, m <= 64 && n <= 64);
+  // the choice without a table too, whose depths go further than the shapes above: a
+  // recorded entry is then no slower than none
+  const Tiling own = automatic_tiling(m, n, batch, p->iters, device_cus());
+  if (std::none_of(cands.begin(), cands.end(), [&](const Candidate& c) {
+        return c.waves == own.shape.waves && c.rows == own.shape.rows_per_thread && c.T == own.T;
+      }))
+    cands.push_back(Candidate{own.shape.waves, own.shape.rows_per_thread, own.T});
   auto run = [&](const Candidate& c) {
     ctv_params q = *p;
     q.fuse = c.T;

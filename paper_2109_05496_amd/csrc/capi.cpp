@@ -182,13 +182,37 @@ static void small_tiling(int m, int n, int batch, int run, int cus, Tiling* out)
     }
 }
 
-ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, int cus, Tiling* out, bool use_tuned, int run) {
+// Default from the tiling sweep on MI355X (2048^2, K = 200): 8 waves x 8 rows
+// (64 x 64 regions) with 8 fused iterations.
+static Tiling default_tiling() {
   Tiling t;
   t.shape.waves = 8;
   t.shape.rows_per_thread = 8;
-  // Default from the tiling sweep on MI355X (2048^2, K = 200): 8 waves x 8 rows
-  // (64 x 64 regions) with 8 fused iterations.
   t.T = 8;
+  return t;
+}
+
+Tiling automatic_tiling(int m, int n, int batch, int total_iters, int cus, int run) {
+  Tiling t = default_tiling();
+  const int iters = run > 0 ? std::min(run, total_iters) : total_iters;
+  small_tiling(m, n, batch, iters, cus, &t);
+  const long long o = 64 - 2 * std::max(1, std::min(8, iters));
+  if (t.shape.waves == 8 && t.shape.rows_per_thread == 8 &&
+      region_as_16x4(((n + o - 1) / o) * ((m + o - 1) / o) * std::min(batch, kPlainChunk), cus)) {
+    t.shape.waves = 16;
+    t.shape.rows_per_thread = 4;
+    // 9 to 11 iterations between checkpoints in one launch instead of two, each
+    // of which would read and write the whole state: 16 x 512^2 and 2048^2 with
+    // 9 / 10 / 11 / 12 / 14 of them take 0.71 / 0.75 / 0.86 / 0.95 / 1.21 of the time
+    // (4096^2 0.71 / 0.78 / 0.92 / 1.08 / 1.39: the halo).
+    if (run >= 9 && run <= 11 && total_iters > run) t.T = run;
+  }
+  clamp_fuse(&t, total_iters);
+  return t;
+}
+
+ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, int cus, Tiling* out, bool use_tuned, int run) {
+  Tiling t = default_tiling();
   if (p->tile_waves != 0 || p->tile_rows != 0) {
     if (p->tile_waves == 0 || p->tile_rows == 0) return fail(CTV_ERR_INVALID_ARG, "tile_waves and tile_rows must be set together");
     t.shape.waves = p->tile_waves == -1 ? 0 : p->tile_waves;   // -1: LDS tile; kSweepShape: row sweep
@@ -197,23 +221,10 @@ ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, int cus, 
       return fail(CTV_ERR_INVALID_ARG, "unsupported tile shape");
   } else if (use_tuned && p->fuse == 0) {
     Tiling tuned;
-    if (tuned_lookup(plain_tune_key(p, batch, m, n), &tuned) && valid_tile_shape(tuned.shape)) {
+    if (tuned_lookup(plain_tune_key(p, batch, m, n), &tuned) && valid_tile_shape(tuned.shape))
       t = tuned;
-    } else {
-      const int iters = run > 0 ? std::min(run, p->iters) : p->iters;
-      small_tiling(m, n, batch, iters, cus, &t);
-      const long long o = 64 - 2 * std::max(1, std::min(8, iters));
-      if (t.shape.waves == 8 && t.shape.rows_per_thread == 8 &&
-          region_as_16x4(((n + o - 1) / o) * ((m + o - 1) / o) * std::min(batch, kPlainChunk), cus)) {
-        t.shape.waves = 16;
-        t.shape.rows_per_thread = 4;
-        // 9 to 11 iterations between checkpoints in one launch instead of two, each
-        // of which would read and write the whole state: 16 x 512^2 and 2048^2 with
-        // 9 / 10 / 11 / 12 / 14 of them take 0.71 / 0.75 / 0.86 / 0.95 / 1.21 of the time
-        // (4096^2 0.71 / 0.78 / 0.92 / 1.08 / 1.39: the halo).
-        if (run >= 9 && run <= 11 && p->iters > run) t.T = run;
-      }
-    }
+    else
+      t = automatic_tiling(m, n, batch, p->iters, cus, run);
   }
   if (p->fuse > 0) t.T = p->fuse;
   clamp_fuse(&t, p->iters);

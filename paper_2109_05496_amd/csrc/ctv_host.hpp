@@ -30,6 +30,8 @@ float step_of(float lam);
 // launch does not cross one).
 ctv_status choose_tiling(const ctv_params* p, int m, int n, int batch, int cus, Tiling* out, bool use_tuned = false,
                          int run = 0);
+// The last of these three.
+Tiling automatic_tiling(int m, int n, int batch, int total_iters, int cus, int run = 0);
 // Compute units of the current device, 0 without one.
 int device_cus();
 // Whether the automatic 64 x 64 region with this many tiles runs as 16 waves x 4 rows.
