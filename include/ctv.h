@@ -28,7 +28,10 @@
  *     default stream). They return after enqueueing work.
  *   - Arguments are validated before any device work; on error nothing is
  *     enqueued and a message is available from ctv_last_error() (thread-local).
- *   - NaN/Inf inputs are not checked; they propagate.
+ *   - NaN/Inf inputs are not checked; they propagate, the same in every tile
+ *     shape and schedule (but see ctv_denoise on tiles outside a support): a NaN or infinite b reaches the pixels that its
+ *     differences reach, a NaN scale of a projection leaves the other entries of
+ *     its group as they are, and entries of a dual that do not exist stay 0.
  *   - FGP state ("dual state") layout: float[batch][2][m][n][4]. Plane 0 holds
  *     q_k, plane 1 holds the extrapolated point r_{k+1} of Algorithm 2, line 5.
  *     Per pixel the four floats are (r1, s1, r2, s2) = (Re Q1, Im Q1, Re Q2,
@@ -171,7 +174,10 @@ ctv_status ctv_tiling(const ctv_params* p, int32_t batch, int32_t m, int32_t n, 
  * (from q_0 = 0, y vanishes at every pixel their differences read), and x = 0
  * there: tiles made only of such pixels are not computed (results are bitwise
  * those of computing them, for finite b). The call then launches two small
- * kernels per tiling that list the other tiles.
+ * kernels per tiling that list the other tiles. Tiles of fewer than 16 output
+ * rows or columns (the automatic choice for many images below about 300 x 300,
+ * whose tiles all run at once) have no list, nor has an
+ * image of at most 64 x 64 pixels under CTV_S_AUTO: all their tiles run.
  * Errors: CTV_ERR_INVALID_ARG (null/negative/out-of-range arguments, unknown
  * kind/constraint, alpha outside [0,1], lambda < 0, non-finite or inside
  * (0, 1e-12) - there the float32 dual step 1/(8 lambda) and the backward's

@@ -1,6 +1,6 @@
 // Host side of ctv_denoise_backward: segment-wise recomputation from the
 // forward checkpoints (fused launches that also store every r_k), the
-// Eq. (18) output adjoint, one reverse-step launch per iteration, and the
+// Eq. (18) output adjoint, launches of up to kMaxRev reverse steps, and the
 // deterministic lambda-gradient reduction.
 #include <hip/hip_runtime.h>
 
@@ -102,8 +102,8 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
     return CTV_OK;
   }
 
-  // Recomputation runs the fused column-tile kernel (default shape), storing
-  // r after every iteration; results do not depend on the tiling. A segment
+  // Recomputation runs the fused column-tile kernel (16 x 4), storing r after
+  // every iteration; results do not depend on the tiling. A segment
   // of up to 12 iterations is recomputed in one launch (16 x 512^2, c = 10:
   // one launch of 9-10 iterations per segment instead of two measured 5 %
   // faster over the whole backward pass).
@@ -148,7 +148,8 @@ ctv_status ctv_denoise_backward(const ctv_params* p, int32_t batch, int32_t m, i
     // With a support the adjoint state stays zero wherever the forward dual
     // does (outside the support, no support pixel below or to the right): the
     // reverse steps run only the tiles holding other pixels, after both
-    // adjoint buffers got their zeros there. The output step runs every tile.
+    // adjoint buffers got their zeros there: the output step, which runs every
+    // tile, stores no B, and later launches read both planes beside a live tile.
     const int* live = nullptr;
     if (support) {
       LiveScanArgs la;

@@ -131,7 +131,7 @@ bool region_as_16x4(long long tiles, int cus) { return cus > 0 && tiles > cus; }
 // Tile shape and fusion depth for `run` iterations where one or two
 // tiles per CU cover the problem. A launch's time is then not bandwidth but the latency of
 // one tile, fixed + step T for T iterations (microseconds, fitted to launches of
-// T = 4 .. 14 on MI355X, within 6 %): smaller tiles start sooner and have fewer
+// T = 4 .. 14 on MI355X): smaller tiles start sooner and have fewer
 // rows to iterate, deeper fusion saves launches, and a larger halo is free as long
 // as the tiles do not outnumber the CUs. The tiles of 4 rows a wave are also
 // considered with two per CU (both resident). These compete against the default
@@ -140,7 +140,12 @@ bool region_as_16x4(long long tiles, int cus) { return cus > 0 && tiles > cus; }
 // 512^2 2.02 -> 1.53, 12 x 150 x 203 2.03 -> 1.68, 700^2 2.23 -> 1.97, 850^2
 // 3.13 -> 2.61, 960^2 3.20 -> 2.80. With more
 // tiles per CU the shapes differ by less than the model's error (1000 x 1501 chosen
-// by it: 293 -> 326 us), so the line is drawn there.
+// by it: 293 -> 326 us), so the line is drawn there. The fit was within 6 % of the tile
+// that it was made on; the present one takes less, by shape (64 x 64, T = 13, us a
+// launch against the table's: 8 x 4 11.8 / 15.2, 12 x 4 14.8 / 17.5, 16 x 4 18.9 / 20.9,
+// 8 x 8 20.4 / 22.1), so shapes within about 10 % of each other may be in the wrong order.
+// An image of one region is priced by the single-tile kernel also where a call cannot
+// take that (checkpoints, CTV_S_STEPS, the phase-retrieval prox).
 static void small_tiling(int m, int n, int batch, int run, int cus, Tiling* out) {
   struct Cost {
     int waves, rows, per_cu;

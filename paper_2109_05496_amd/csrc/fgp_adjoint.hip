@@ -161,8 +161,9 @@ __device__ __forceinline__ double block_sum_d(double v, double* red) {
 // tiles at the image's border load through row buffers with zero steps instead of
 // branches and selects. The rows' f64 sums keep a branch of their own (the empty
 // asm): as selects, the whole step became one block and spilled 28 registers.
-// Measured before -> after: backward pass of 3 x 201 x 333 (border tiles) 395 -> 320 us
-// with its forward, of 16 x 512^2, 50 iterations, 3041 -> 2959 us.
+// Measured before -> after: backward pass of 16 x 512^2, 50 iterations, 3041 -> 2959 us;
+// forward and backward of 3 x 201 x 333 (border tiles), 20 iterations, 205 -> 164 us with the
+// forward tile's steps.
 //
 // J.steps reverse steps k, k-1, ... on one tile with halo H >= steps + 1: a step
 // reads (A, B) one pixel and r_k two pixels around each point it updates, so

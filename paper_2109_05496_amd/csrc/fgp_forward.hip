@@ -179,8 +179,8 @@ constexpr int waves_per_simd(int NW, int P) { return NW == 16 && P == 4 ? 8 : 4;
 
 // BORDER = false is the path for tiles whose region lies at least one pixel
 // inside the image on every side: no neighbour there leaves the image. BORDER =
-// true handles the others (every tile of an image below about 200 pixels a
-// side) with the same instructions per pixel: loads and stores go through
+// true handles the others (every 64 x 64 region of an image below 105 pixels a
+// side at a halo of 8, below 93 at 12) with the same instructions per pixel: loads and stores go through
 // bounds-checked row buffers (zeros outside the image, all rows in flight at
 // once; a branch per row made each wait for the one before), and the step of a
 // difference that leaves the image is 0, which keeps its dual at 0 (eight
